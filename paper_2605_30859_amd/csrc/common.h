@@ -11,6 +11,7 @@ typedef uint16_t bf16_t;                       // raw bfloat16 bits
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 constexpr int kPage = 16;
@@ -25,6 +26,14 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   if ((b & 0x7fffffffu) > 0x7f800000u) return (bf16_t)0x7fc0;
   uint32_t lsb = (b >> 16) & 1u;
   return (bf16_t)((b + 0x7fffu + lsb) >> 16);
+}
+
+// Two floats rounded to nearest even by the hardware's conversion, the first in
+// the low half (equal to f32_to_bf16 except for a NaN's sign and payload).
+__device__ __forceinline__ uint32_t f32_to_bf16x2(float a, float b) {
+  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
 
 // Philox4x32-10 (Salmon et al., SC'11): 10 rounds of two 32x32->64 products

@@ -355,8 +355,8 @@ hipError_t launch_moe_ffn(const MoeArgs& a, hipStream_t st, bool* normed) {
   const float* lg = n_split > 1 ? (const float*)a.gemm_ws : a.logits;
   const int64_t zs = (int64_t)a.n_rows * a.E_pad;
   const dim3 gtk((a.n_rows + 3) / 4), btk(256);
-  const GroupedPlan plan_gu = grouped_plan((int64_t)a.n_rows * a.k, a.E, true);
-  const GroupedPlan plan_dn = grouped_plan((int64_t)a.n_rows * a.k, a.E, false);
+  const GroupedPlan plan_gu = grouped_plan((int64_t)a.n_rows * a.k, a.E, true, (int64_t)a.n_rows * a.d * 2);
+  const GroupedPlan plan_dn = grouped_plan((int64_t)a.n_rows * a.k, a.E, false, 0);
   const bool dbg = a.force_ids || a.own_ids_out || a.used_p_out;
 #define DARTS_TOPK(NPL)                                                                          \
   if (dbg)                                                                                       \

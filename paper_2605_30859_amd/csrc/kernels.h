@@ -74,7 +74,8 @@ hipError_t launch_gather_rows(const float* src, const int32_t* rows, int n, int 
 // (grouped_plan), e << 16 | tile, *n_mtiles of them (device values).
 // N % 128 == 0, K % 64 == 0.  packed_w: W is in the strip layout of
 // launch_pack_strips (ldw = K; SwiGLU epilogue only).
-constexpr int kGroupedTileRows = 128;      // largest row tile
+constexpr int kGroupedTileRows = 256;      // row tile of large batches (the prefill)
+constexpr int kGroupedTileRowsFar = 128;   // the same when gathered rows lie beyond 32-bit offsets
 constexpr int kGroupedTileRowsGU = 96;     // gate/up row tile of large decode batches
 constexpr int kGroupedTileRowsMin = 64;    // smallest row tile (sizes the tile lists)
 // Plan for n_pairs routed (row, expert) pairs over E experts: the row tile
@@ -82,8 +83,9 @@ constexpr int kGroupedTileRowsMin = 64;    // smallest row tile (sizes the tile 
 // few rows (decode batches: the weights are streamed and half-empty 128-row
 // tiles would double the operand traffic), 96-row tiles for the gate/up
 // projection from 48 rows per expert (so an expert's weights are not
-// streamed twice), 128-row tiles for large batches (the prefill: more reuse
-// of each weight tile).  wdirect: the gate/up weights go straight into MFMA
+// streamed twice), 256-row tiles of the alternating groups for large batches
+// (the prefill; gathered_bytes, the size of the matrix that A rows are gathered
+// from, has to fit their 32-bit offsets, else 128-row tiles).  wdirect: the gate/up weights go straight into MFMA
 // registers (from 2 rows per expert up to the prefill), otherwise through
 // the LDS tile ring.  nt_w: the weights are loaded non-temporal (gate/up in
 // every decode batch; down while no expert needs a second row tile, whose
@@ -93,7 +95,7 @@ struct GroupedPlan {
   bool wdirect;
   bool nt_w;
 };
-GroupedPlan grouped_plan(int64_t n_pairs, int E, bool gate_up);
+GroupedPlan grouped_plan(int64_t n_pairs, int E, bool gate_up, int64_t gathered_bytes);
 hipError_t launch_gemm_grouped(const void* A, int lda, const void* W, int64_t w_stride, int ldw,
                                void* C, int ldc, int N, int K, int epi, const int32_t* g_off,
                                const int32_t* g_cnt, const int32_t* mtiles, const int32_t* n_mtiles,

@@ -101,3 +101,36 @@ def test_gemm_lm_head_full_size_sampled_rows():
 def test_gemm_prefill_size_sampled_rows():
     """Prefill-sized M (32 prompts x 512 tokens) on the QKV shape; sampled rows."""
     _run(16384, 6144, 4096, 0, sample_rows=np.array([0, 1, 127, 128, 8191, 16000, 16383]))
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(4133, 6144, 512, 0), (4096, 4096, 256, 2), (8203, 6144, 256, 1),
+                                       (4133, 8192, 1024, 3), (8195, 4096, 256, 3), (300, 24576, 4096, 3),
+                                       (1030, 4096, 4096, 2), (2049, 4096, 12288, 2), (257, 24576, 256, 1)])
+def test_gemm_large_tiles_every_row(M, N, K, epi):
+    """256-row tiles on persistent blocks: several tiles per block, the last row
+    tile nearly empty or full, the shortest K ranges, with and without a split.
+    Every row against float64; rows past M are not written.  Tolerances: fp32
+    sums of K products of order 1/sqrt(K), K*2^-24 at worst; bf16 results 2^-8,
+    and the SwiGLU product's inputs as much again."""
+    print(f"gemm large tiles M={M} N={N} K={K} epi={epi}", flush=True)
+    B = _b()
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    a = torch.randn(M, K, device=DEV, generator=g).bfloat16()
+    w = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).bfloat16()
+    cols = N // 2 if epi == 3 else N
+    dt = torch.bfloat16 if epi in (1, 3) else torch.float32
+    out = torch.full((M + 256, cols), 7.0, dtype=dt, device=DEV)
+    init = out[:M].double()
+    ws = torch.empty(max(B.darts_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8, device=DEV)
+    B.darts_gemm(a, w, out, M, N, K, B.DARTS_BF16, epi, ws)
+    torch.cuda.synchronize()
+    ref = a.double() @ w.double().T
+    if epi == 3:
+        ref = ref.view(M, N // 32, 2, 16)
+        ref = (torch.nn.functional.silu(ref[:, :, 0]) * ref[:, :, 1]).reshape(M, cols)
+    elif epi == 2:
+        ref = ref + init
+    err = (out[:M].double() - ref).abs()
+    tol = 2 ** -8 * ref.abs() + 1e-3 if epi in (1, 3) else K * 2.0 ** -24 * (ref.abs() + 1.0)
+    assert bool((err <= tol).all()), (M, N, K, epi, float((err - tol).max()))
+    assert bool((out[M:] == 7.0).all())

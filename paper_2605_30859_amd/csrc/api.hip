@@ -582,8 +582,9 @@ int darts_init(const darts_model_cfg* model, int32_t m, int32_t k, const darts_r
   c->gemm_ws_bytes = gemm_ws_need(c);
   A(&c->gemm_ws, c->gemm_ws_bytes);
   c->share_prefix = c->bf16 && c->m > 1 && c->pp > 0 && (c->rc.flags & DARTS_FLAG_SHARED_PREFIX);
-  c->attn_ws_bytes = std::max(attn_workspace_bytes(c->n_traj, c->hq, c->hkv, c->hd, c->Lp + c->cap),
-                              attn_workspace_bytes(rows_pf, c->hq, c->hkv, c->hd, c->Lp));
+  c->attn_ws_bytes = attn_workspace_bytes(c->n_traj, c->hq, c->hkv, c->hd, c->Lp + c->cap);
+  if (!c->bf16)   // the bf16 prefill kernel needs none
+    c->attn_ws_bytes = std::max(c->attn_ws_bytes, attn_workspace_bytes(rows_pf, c->hq, c->hkv, c->hd, c->Lp));
   if (c->share_prefix)
     c->attn_ws_bytes = std::max(c->attn_ws_bytes, attn_shared_workspace_bytes(c->n_traj, c->hq, c->hkv,
                                                                                c->hd, c->Lp + c->cap, c->pp));
@@ -729,6 +730,11 @@ static int run_attention(darts_ctx* c, int layer, int n_rows, const int32_t* row
                                       c->n_traj, c->m, c->pp, layer == 0, ctx_base, n_rows, c->hq,
                                       c->hkv, c->hd, c->attn,
                                       c->attn_ws, c->attn_ws_bytes, c->st, e0, e1, c->dcnt + 8));
+    return DARTS_OK;
+  }
+  if (c->bf16 && ctx_mod > 0) {   // the prefill: every prompt's own positions
+    HIPCHK(c, launch_attention_prefill(c->q, kp, vp, c->n_pages, c->page_table, (int64_t)c->m * c->max_pages, c->P,
+                                       c->Lp, c->hq, c->hkv, c->hd, c->attn, c->st));
     return DARTS_OK;
   }
   HIPCHK(c, launch_attention(c->q, kp, vp, c->n_pages, c->page_table, c->max_pages, row_pt, nullptr,

@@ -18,6 +18,8 @@
 // vectors (the per-row kernel fills only G of its 16 MFMA rows); the per-row
 // kernel then covers the keys after the prefix, starting from the prefix
 // partials.
+//
+// The prefill of bf16 models has a kernel of its own (attn_prefill_kernel).
 #include <math.h>
 
 #include <algorithm>
@@ -463,6 +465,224 @@ __global__ void __launch_bounds__(256) attn_prefix_kernel(AttnPrefixArgs A) {
       if (col == 0) A.pre_ml[idx] = make_float2(acc.m[i], l);
     }
   }
+}
+
+// ------------------------------------------------------------------ prefill
+// Causal attention of whole prompts (bf16): query position t of a prompt
+// attends to its keys 0..t, which lie in the prompt's pages.
+//
+// Block = 4 wavefronts over (prompt, kv head, run of query vectors).  The
+// query vectors of a (prompt, kv head) are its positions times the G heads that
+// share the kv head, position-major, whatever G is; a wavefront takes NT tiles
+// of 16.  Keys and values pass through LDS in stages of 64 keys (4 pages,
+// one copied by each wavefront with direct 16-byte LDS loads, the next stage
+// while this one is computed), so each is read once per block and not once per
+// query.  Products are transposed, so that a lane's scores belong to one query:
+//   S^T[keys x 16] = K . Q^T     two tiles of 16 keys per 32 keys; row 4q+i of
+//                                tile u is key 8q + 4u + i
+//   P^T            = 2^(c S^T - m), in fp32, rounded to bf16: the lane's eight
+//                                weights are the eight keys of its quad, which
+//                                is the next product's operand as it stands
+//   O^T[dims x 16] += V^T . P^T  two tiles of 16 dims per 32 dims; row 4q+i of
+//                                tile u is dim 8q + 4u + i, so that a lane ends
+//                                with 8 consecutive dims
+//   l              += 1 . P^T    the denominator: the sum of the rounded weights
+// The running maximum m is only moved on (and O and l rescaled) when a score
+// exceeds it by more than 8 in the exponent: weights then stay below 2^8, and
+// the ratio O / l is the same.
+//
+// Bound by VALU and matrix issue (the exponentials of a 16 x 32 tile take about
+// as long as its products), hence two blocks per CU.  64 prompts x 512 tokens,
+// 32/4 heads x 128: 270 us per layer (137 GFLOP, 510 TFLOP/s), against 1600 us
+// for the decode kernel with one row per query position, which reads every key
+// once per query.  With 2 or 4 tiles per wavefront: 288 and 409 us (4 spill
+// past 256 registers); with the maximum moved on at every change: 286 us.
+struct PrefillArgs {
+  const bf16_t* q; const bf16_t* kpool; const bf16_t* vpool;
+  const int32_t* page_table; int64_t pt_step;   // page list of prompt i: page_table + i * pt_step
+  int64_t n_pages;
+  int n_prompts, len, hq, hkv;                  // len: positions per prompt, a multiple of 16
+  bf16_t* out;
+};
+constexpr int kPreWaves = 4, kPreKeys = 64;     // wavefronts per block (one copies one page), keys per stage
+constexpr float kPreLag = 8.0f;                 // how far (log2) scores may exceed the running maximum
+
+template <int HD, int NT>
+__global__ void __launch_bounds__(64 * kPreWaves, 2) attn_prefill_kernel(PrefillArgs A) {
+  constexpr int NKK = HD / 32;                  // 32-dim blocks: K steps of S, dim pairs of tiles of O
+  constexpr int PB = kPage * HD;                // elements of a page of one kv head (K or V)
+  __shared__ __attribute__((aligned(16))) bf16_t smem[2][2][kPreWaves * PB];   // [stage][K | V][page]
+  static_assert(kPreWaves * kPage == kPreKeys, "a wavefront copies a page");
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int quad = lane >> 4, col = lane & 15;
+  const int G = A.hq / A.hkv;
+  const int pairs = A.n_prompts * A.hkv;
+  const int nvec = A.len * G, ntile = (int)(gridDim.x / pairs);
+  // longest runs (last positions) first
+  const int run = ntile - 1 - (int)(blockIdx.x / pairs), pair = (int)(blockIdx.x % pairs);
+  const int prompt = pair / A.hkv, kvh = pair % A.hkv;
+  const int v0 = (run * kPreWaves + w) * NT * 16;           // this wavefront's query vectors
+  const int vend = min((run + 1) * kPreWaves * NT * 16, nvec);
+  const int n_stage = ((vend - 1) / G) / kPreKeys + 1;      // stages the block needs
+  const int tlast = v0 < nvec ? min(v0 + NT * 16 - 1, nvec - 1) / G : -1;   // the wavefront's last position
+
+  bf16x8_t qb[NT][NKK];
+  int t[NT];                                                // position of the lane's query
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int v = min(v0 + n * 16 + col, nvec - 1);
+    t[n] = v / G;
+    const bf16_t* src = A.q + (((int64_t)prompt * A.len + t[n]) * A.hq + kvh * G + (v - t[n] * G)) * HD + quad * 8;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) qb[n][kk] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(src + 32 * kk));
+  }
+  // Copy of page w of a stage.  LDS holds K's 16-byte chunk (slot, dims 8c..)
+  // of a 32-dim block at chunk slot*4 + (c ^ (slot/4) ^ (page parity)), and V's
+  // (dim) at chunk dim ^ 4*(dim/16 odd): the 16 lanes of a quad then read 256
+  // bytes that lie in different banks.
+  const int kslot = lane >> 2, kch = (lane & 3) ^ (kslot >> 2) ^ (w & 1);
+  const int ksrc = kslot * 32 + kch * 8, vsrc = (lane ^ (((lane >> 4) & 1) << 2)) * 8;
+  const int32_t* pt = A.page_table + prompt * A.pt_step;
+  const int last_page = A.len / kPage - 1;
+  int ids = 0;                                              // lane i: this wavefront's page of stage i (mod 64)
+  auto copy = [&](int stage, int buf) {
+    if ((stage & 63) == 0) ids = pt[min((stage + lane) * kPreWaves + w, last_page)];
+    const int id = __builtin_amdgcn_readlane(ids, stage & 63);
+    const int64_t page = min((int64_t)max(id, 0), A.n_pages - 1);
+    const bf16_t* k = A.kpool + (page * A.hkv + kvh) * PB;
+    const bf16_t* v = A.vpool + (page * A.hkv + kvh) * PB;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      __builtin_amdgcn_global_load_lds((const void*)(k + kk * 512 + ksrc),
+                                       (__attribute__((address_space(3))) void*)(&smem[buf][0][w * PB + kk * 512]), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const void*)(v + kk * 512 + vsrc),
+                                       (__attribute__((address_space(3))) void*)(&smem[buf][1][w * PB + kk * 512]), 16, 0, 0);
+    }
+  };
+  // fragment offsets in a 32-key half of a stage (pages 2*half, 2*half + 1):
+  // key 8*(col/4) + 4u + col%4 and dim 8*(col/4) + 4u + col%4 of a block of 32
+  int koff[2], voff[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int x = 8 * (col >> 2) + 4 * u + (col & 3), slot = x & 15, pg = x >> 4;
+    koff[u] = pg * PB + slot * 32 + ((quad ^ (slot >> 2) ^ pg) * 8);
+    voff[u] = (quad >> 1) * PB + ((quad & 1) * HD + (x ^ (((x >> 4) & 1) << 2))) * 8;
+  }
+
+  f32x4_t O[NT][NKK][2], l[NT];
+  float m[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    m[n] = -INFINITY;
+    l[n] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < NKK; ++b) O[n][b][0] = O[n][b][1] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  }
+  const u32x4_t ones_bits = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, ones_bits);
+  const float c = 1.4426950408889634f / sqrtf((float)HD);   // scores to exponents of 2
+
+  copy(0, 0);
+  for (int st = 0; st < n_stage; ++st) {
+    // this stage's copies (this wavefront's) have landed, then everybody's; all
+    // reads of the other buffer were done before this barrier
+    __builtin_amdgcn_s_waitcnt(0xf70);                      // vmcnt(0)
+    __syncthreads();
+    if (st + 1 < n_stage) copy(st + 1, (st + 1) & 1);
+    const bf16_t* sk = smem[st & 1][0];
+    const bf16_t* sv = smem[st & 1][1];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int k0 = st * kPreKeys + half * 32;
+      if (k0 > tlast) break;
+      f32x4_t S[NT][2];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) S[n][0] = S[n][1] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8_t kf = *(const bf16x8_t*)(sk + half * 2 * PB + kk * 512 + koff[u]);
+#pragma unroll
+          for (int n = 0; n < NT; ++n) S[n][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qb[n][kk], S[n][u], 0, 0, 0);
+        }
+      bf16x8_t pf[NT];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        if (k0 + 31 > v0 / G) {                             // some query of the wavefront ends in these keys
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (k0 + 8 * quad + 4 * u + i > t[n]) S[n][u][i] = -INFINITY;
+        }
+        float mx = fmaxf(fmaxf(fmaxf(S[n][0][0], S[n][0][1]), fmaxf(S[n][0][2], S[n][0][3])),
+                         fmaxf(fmaxf(S[n][1][0], S[n][1][1]), fmaxf(S[n][1][2], S[n][1][3])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
+        if (__any(mx > m[n] + kPreLag)) {
+          const float mnew = fmaxf(m[n], mx);
+          const float alpha = exp2f(m[n] - mnew);
+          m[n] = mnew;
+          l[n] *= alpha;
+#pragma unroll
+          for (int b = 0; b < NKK; ++b) { O[n][b][0] *= alpha; O[n][b][1] *= alpha; }
+        }
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(S[n][e >> 2][e & 3], c, -m[n]));
+        const u32x4_t pk = {f32_to_bf16x2(p[0], p[1]), f32_to_bf16x2(p[2], p[3]), f32_to_bf16x2(p[4], p[5]),
+                            f32_to_bf16x2(p[6], p[7])};
+        pf[n] = __builtin_bit_cast(bf16x8_t, pk);
+      }
+#pragma unroll
+      for (int n = 0; n < NT; ++n) l[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[n], l[n], 0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NKK; ++b)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8_t vf = *(const bf16x8_t*)(sv + half * 2 * PB + b * 256 + voff[u]);
+#pragma unroll
+          for (int n = 0; n < NT; ++n) O[n][b][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[n], O[n][b][u], 0, 0, 0);
+        }
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int v = v0 + n * 16 + col;
+    if (v >= nvec) continue;
+    const float inv = 1.0f / l[n][0];
+    bf16_t* dst = A.out + (((int64_t)prompt * A.len + t[n]) * A.hq + kvh * G + (v - t[n] * G)) * HD + quad * 8;
+#pragma unroll
+    for (int b = 0; b < NKK; ++b) {
+      const f32x4_t x = O[n][b][0] * inv, y = O[n][b][1] * inv;
+      *(u32x4_t*)(dst + 32 * b) = (u32x4_t){f32_to_bf16x2(x[0], x[1]), f32_to_bf16x2(x[2], x[3]),
+                                            f32_to_bf16x2(y[0], y[1]), f32_to_bf16x2(y[2], y[3])};
+    }
+  }
+}
+
+template <int HD, int NT>
+static void attn_prefill_go(const PrefillArgs& a, hipStream_t st) {
+  const int64_t tiles = ((int64_t)a.len * (a.hq / a.hkv) + kPreWaves * NT * 16 - 1) / (kPreWaves * NT * 16);
+  hipLaunchKernelGGL((attn_prefill_kernel<HD, NT>), dim3((unsigned)(tiles * a.n_prompts * a.hkv)), dim3(64 * kPreWaves),
+                     0, st, a);
+}
+
+hipError_t launch_attention_prefill(const void* q, const void* k_pool, const void* v_pool, int64_t n_pages,
+                                    const int32_t* page_table, int64_t pt_step, int n_prompts, int len, int hq,
+                                    int hkv, int hd, void* out, hipStream_t st) {
+  if (n_prompts <= 0) return hipSuccess;
+  if (len < kPage || len % kPage || hkv < 1 || hq % hkv || n_pages < 1) return hipErrorInvalidValue;
+  PrefillArgs a;
+  a.q = (const bf16_t*)q; a.kpool = (const bf16_t*)k_pool; a.vpool = (const bf16_t*)v_pool;
+  a.page_table = page_table; a.pt_step = pt_step; a.n_pages = n_pages;
+  a.n_prompts = n_prompts; a.len = len; a.hq = hq; a.hkv = hkv; a.out = (bf16_t*)out;
+  if (hd == 128) attn_prefill_go<128, 3>(a, st);
+  else if (hd == 64) attn_prefill_go<64, 4>(a, st);
+  else if (hd == 32) attn_prefill_go<32, 4>(a, st);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 // fp32 attention (fp32 models): one wavefront per (row, q head, chunk).

@@ -115,6 +115,12 @@ hipError_t launch_attention(const void* q, const void* k_pool, const void* v_poo
                             int ctx_base, int n_rows, int hq, int hkv, int hd, int max_ctx,
                             bool bf16, void* out, void* ws, size_t ws_bytes, hipStream_t st,
                             hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Causal attention of n_prompts prompts of len positions (a multiple of 16),
+// bf16: row i*len + t of q and out is position t of prompt i, whose pages are
+// the first len/16 entries of page_table + i * pt_step.
+hipError_t launch_attention_prefill(const void* q, const void* k_pool, const void* v_pool, int64_t n_pages,
+                                    const int32_t* page_table, int64_t pt_step, int n_prompts, int len, int hq,
+                                    int hkv, int hd, void* out, hipStream_t st);
 // Shared-prefix decode attention (bf16): every row has context ctx; row r
 // uses page-table row row_traj[r] (clamped into [0, pt_rows) when pt_rows >
 // 0); consecutive rows of one group (row_traj[r] / m) share their first

@@ -13,19 +13,23 @@
 //
 // Filtered argmax.  g_i is defined by the library's exact float32 logarithm
 // (two per element, each with a correctly rounded division), which would
-// dominate the kernel's arithmetic.  The scan instead scores every element
-// with a fast map (two hardware log2 evaluations) whose distance from the
-// exact map is at most kGumbelFastBound over all 2^23 possible u (checked
-// exhaustively on the device by the test suite), and each thread keeps its
-// two best fast scores.  If they are further apart than twice the bound on
-// |fast score - exact score| (noise error plus the float32 roundings of the
-// two sums), the thread's exact winner is its fast winner, whose exact score
-// is then computed once; otherwise (a near tie, probability ~1e-5 per thread)
-// the thread re-scans its elements with the exact map.  The token is
-// therefore the exact-map argmax, bit for bit, in every case.
+// dominate the kernel's arithmetic.  The scan instead drops every element that
+// a threshold shows to be no winner (sample_kernel) and takes the exact score
+// of the few that are left, so the token is the exact-map argmax, bit for bit.
+// The first threshold comes from a fast map (two hardware log2 evaluations)
+// whose distance from the exact map is at most kGumbelFastBound over all 2^23
+// possible u (checked exhaustively on the device by the test suite).
+//
+// Bound by VALU issue: Philox (17 64-bit products per 4 logits), one
+// exponential per logit, the softmax sums.  1024 x 151936 bf16 logits take
+// 135 us (about 95 vector instructions per 4 logits and lane, 17 of them 64-bit
+// products and 4 exponentials), against 325 us when every element's fast score was evaluated,
+// each thread's best two compared and the division by T computed for T = 1 too.
 #include <math.h>
 
 #include <algorithm>
+#include <cstring>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -55,19 +59,24 @@ __device__ __forceinline__ Best best_merge(Best a, Best b) {
   return a;
 }
 
+// Four consecutive logits as they are in memory, and as floats.
 template <bool BF16>
-__device__ __forceinline__ void load4(const void* row, int j, float z[4]) {
-  if (BF16) {
-    const uint2 v = ((const uint2*)row)[j];
+struct Raw4 {
+  uint2 v;
+  __device__ __forceinline__ void load(const void* row, int j) { v = ((const uint2*)row)[j]; }
+  __device__ __forceinline__ void get(float z[4]) const {
     z[0] = __uint_as_float(v.x << 16);
     z[1] = __uint_as_float(v.x & 0xffff0000u);
     z[2] = __uint_as_float(v.y << 16);
     z[3] = __uint_as_float(v.y & 0xffff0000u);
-  } else {
-    const float4 v = ((const float4*)row)[j];
-    z[0] = v.x; z[1] = v.y; z[2] = v.z; z[3] = v.w;
   }
-}
+};
+template <>
+struct Raw4<false> {
+  float4 v;
+  __device__ __forceinline__ void load(const void* row, int j) { v = ((const float4*)row)[j]; }
+  __device__ __forceinline__ void get(float z[4]) const { z[0] = v.x; z[1] = v.y; z[2] = v.z; z[3] = v.w; }
+};
 
 // Fast Gumbel map: -ln(-ln u) from two hardware log2 evaluations (the only
 // approximation; products by ln 2 in float32).  u in [2^-24, 1 - 2^-24]
@@ -155,34 +164,90 @@ __device__ __forceinline__ void finish_row(const SampleArgs& a, int r, const Row
 // vocabulary.  With one part the block finishes the row; with several it
 // writes its partial (softmax state, winner) and the finalize kernel merges
 // the parts.
-template <bool BF16, bool STATEFUL>
-__global__ void __launch_bounds__(256) sample_kernel(SampleArgs a) {
-  __shared__ SoftState ss[4];
-  __shared__ Best sb[4];
+//
+// The scan filters the elements by a threshold T, the largest exact score (or
+// a bound just below a fast one) that the block has seen so far: an element can
+// only be the winner if z + g >= T.  Since -ln u >= 1 - u, that needs
+//   1 - u <= exp(z - T) = e^(z-m) * e^(m-T),
+// and e^(z-m) is at hand from the softmax sums, so the test is a conversion, a
+// fused multiply-add and a comparison per element instead of two logarithms.
+// Whatever passes (about one element in a few thousand once T has settled) gets
+// its exact score.  kSlackAbs + kSlackRel |T| on the exponent covers the
+// float32 errors: the noise map's 2e-6, the rounding of z + g (2^-24 |T|), of
+// both exponentials' arguments (at most 20 in magnitude where the outcome
+// matters: g <= 16.7 and T >= m - 2.9) and of the words' conversion (kWordSlack).
+constexpr float kSlackAbs = 1.953125e-03f;       // 2^-9
+constexpr float kSlackRel = 4.76837158203125e-07f;   // 2^-21
+constexpr float kWordSlack = 1024.0f;            // in units of the 32-bit word, which rounds to 256
+
+// float <-> int keys of the same order (NaN never gets here)
+__device__ __forceinline__ int order_key(float f) {
+  const int b = __float_as_int(f);
+  return b ^ ((b >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float key_order(int k) { return __int_as_float(k ^ ((k >> 31) & 0x7fffffff)); }
+
+// Division by the temperature: none (1), by a correctly rounded reciprocal with
+// one fused correction, or the full division.  q = z y with y = RN(1/T), then
+// RN(q + (z - q T) y) is the correctly rounded quotient while nothing
+// over- or underflows and T's significand is not all ones (Markstein's
+// theorem); other temperatures, and groups with a logit outside
+// [2^-100, 2^100], take the full division, which costs as much as Philox.
+enum { T_ONE, T_RECIP, T_FULL };
+template <bool BF16, bool STATEFUL, int THREADS, int TMODE>
+__global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
+  constexpr int NW = THREADS / 64;
+  __shared__ SoftState ss[NW];
+  __shared__ Best sb[NW];
+  __shared__ int s_thr;                          // the block's T, as an order key
   const int parts = a.parts > 1 ? a.parts : 1;
   const int r = blockIdx.x / parts, part = blockIdx.x - r * parts;
   const int tid = threadIdx.x;
+  if (tid == 0) s_thr = (int)0x807fffff;          // -INFINITY
+  __syncthreads();
   const RowCtx c = row_ctx<BF16, STATEFUL>(a, r);
   const int g = c.g, step = c.step;
   const uint32_t gc = (uint32_t)g + (uint32_t)a.traj_base;   // the counter's (global) trajectory id
   const void* row = c.row;
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  const bool tscale = a.temperature != 1.0f;
   SoftState st = {-INFINITY, 0.f, 0.f};
-  float b1 = -INFINITY, b2 = -INFINITY;   // this thread's two best fast scores
-  int i1 = 0x7fffffff;                     // index of the best
+  Best best = {-INFINITY, 0x7fffffff};           // this thread's best exact score
   const int n4 = a.vocab >> 2;
   const int span = (n4 + parts - 1) / parts;
   const int jb = part * span, je = min(n4, jb + span);
-  for (int j = jb + tid; j < je; j += 256) {
+  constexpr int kNone = (int)0x807fffff;         // order_key(-INFINITY)
+  int thr = kNone;                               // T as this thread knows it
+  float lim = 0.f;                               // 2^32 e^(m - T + slack), finite; 0 while m is -inf
+  auto set_lim = [&]() {
+    const float T = key_order(thr);
+    const float x = 4294967296.0f * __expf(st.m - T + (kSlackAbs + kSlackRel * fabsf(T)));
+    lim = st.m == -INFINITY ? 0.f : fminf(x, 3.0e38f);      // also when x is NaN (an infinite logit)
+  };
+  auto block_thr = [&]() { return __hip_atomic_load(&s_thr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  Raw4<BF16> next;
+  if (jb + tid < je) next.load(row, jb + tid);
+  for (int j = jb + tid; j < je; j += THREADS) {
     float z[4];
-    load4<BF16>(row, j, z);
-    if (tscale) {
+    next.get(z);
+    if (j + THREADS < je) next.load(row, j + THREADS);
+    if constexpr (TMODE != T_ONE) {
+      constexpr float kBig = 1.2676506e+30f, kSmall = 7.8886091e-31f;   // 2^100, 2^-100
+      const float hi = fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3])));
+      const float lo = fminf(fminf(fabsf(z[0]), fabsf(z[1])), fminf(fabsf(z[2]), fabsf(z[3])));
+      if (TMODE == T_RECIP && hi <= kBig && lo >= kSmall) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) z[e] = __fdiv_rn(z[e], a.temperature);
+        for (int e = 0; e < 4; ++e) {
+          const float q = z[e] * a.inv_temperature;
+          z[e] = fmaf(fmaf(-q, a.temperature, z[e]), a.inv_temperature, q);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = __fdiv_rn(z[e], a.temperature);
+      }
     }
     const Philox4 p = philox4x32_10((uint32_t)j, gc, (uint32_t)step, kTagSample, k0, k1);
-    float lm = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+    float top = 0.f;     // largest of the elements' word + lim e^(z-m)
+    const float lm = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
     if (lm > st.m) {
       if (st.s > 0.f) {   // rescale the running sums to the new maximum
         const float sc = __expf(st.m - lm);
@@ -190,6 +255,22 @@ __global__ void __launch_bounds__(256) sample_kernel(SampleArgs a) {
         st.s = st.s * sc;
       }
       st.m = lm;
+      set_lim();
+      if (lm == INFINITY) top = 4294967296.0f;   // only the first infinite logit can win
+    }
+    int known = block_thr();
+    if (known == kNone) {
+      // nothing seen yet: T from the fast scores of this group, less their error
+      float f = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f = fmaxf(f, z[e] + gumbel_fast(open_unit(p.x[e])));
+      f -= 2.0f * (kGumbelFastBound + 2.384185791015625e-07f * fabsf(f));
+      if (f > -INFINITY) atomicMax(&s_thr, order_key(f));
+      known = block_thr();
+    }
+    if (known > thr) {
+      thr = known;
+      set_lim();
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -199,33 +280,16 @@ __global__ void __launch_bounds__(256) sample_kernel(SampleArgs a) {
       const float ez = __expf(d);
       st.s += ez;
       st.t = fmaf(ez, d, st.t);
-      const float sf = z[e] + gumbel_fast(open_unit(p.x[e]));
-      const bool c1 = sf > b1, c2 = sf > b2;
-      b2 = c1 ? b1 : (c2 ? sf : b2);
-      b1 = c1 ? sf : b1;
-      i1 = c1 ? 4 * j + e : i1;
+      top = fmaxf(top, fmaf(ez, lim, (float)p.x[e]));
     }
-  }
-  // exact score of this thread's winner, or an exact re-scan on a near tie
-  Best best = {-INFINITY, 0x7fffffff};
-  const float margin =
-      2.0f * (kGumbelFastBound + 2.384185791015625e-07f * fmaxf(fabsf(b1), fabsf(b2)));   // 2^-22 |s|
-  if (b1 - b2 > margin) {
-    const int j = i1 >> 2, e = i1 & 3;
-    const Philox4 p = philox4x32_10((uint32_t)j, gc, (uint32_t)step, kTagSample, k0, k1);
-    best.v = logit_at<BF16>(row, i1, tscale, a.temperature) + gumbel_of(open_unit(p.x[e]));
-    best.i = i1;
-  } else {
-    for (int j = jb + tid; j < je; j += 256) {
-      float z[4];
-      load4<BF16>(row, j, z);
-      const Philox4 p = philox4x32_10((uint32_t)j, gc, (uint32_t)step, kTagSample, k0, k1);
+    if (top >= 4294967296.0f - kWordSlack) {
+      const float before = best.v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float zz = tscale ? __fdiv_rn(z[e], a.temperature) : z[e];
-        const float sc = zz + gumbel_of(open_unit(p.x[e]));
+        const float sc = z[e] + gumbel_of(open_unit(p.x[e]));
         if (sc > best.v) { best.v = sc; best.i = 4 * j + e; }
       }
+      if (best.v > before) atomicMax(&s_thr, order_key(best.v));
     }
   }
   // wavefront merge
@@ -239,8 +303,16 @@ __global__ void __launch_bounds__(256) sample_kernel(SampleArgs a) {
   if ((tid & 63) == 0) { ss[tid >> 6] = st; sb[tid >> 6] = best; }
   __syncthreads();
   if (tid != 0) return;
-  st = soft_merge(soft_merge(ss[0], ss[1]), soft_merge(ss[2], ss[3]));
-  best = best_merge(best_merge(sb[0], sb[1]), best_merge(sb[2], sb[3]));
+  // pairs of wavefronts, then pairs of pairs
+#pragma unroll
+  for (int o = 1; o < NW; o <<= 1)
+#pragma unroll
+    for (int i = 0; i + o < NW; i += 2 * o) {
+      ss[i] = soft_merge(ss[i], ss[i + o]);
+      sb[i] = best_merge(sb[i], sb[i + o]);
+    }
+  st = ss[0];
+  best = sb[0];
   if (parts > 1) {
     SamplePart o;
     o.m = st.m; o.s = st.s; o.t = st.t; o.v = best.v; o.i = best.i;
@@ -290,22 +362,39 @@ hipError_t launch_sample(const SampleArgs& a0, hipStream_t st) {
   a.parts = a.part_out ? sample_parts(a.n_rows, a.vocab) : 1;
   if (a.parts > 1 && (int64_t)a.n_rows * a.parts > a.part_cap) a.parts = 1;
   const bool stateful = a.gen != nullptr;
-  const dim3 grid((unsigned)(a.n_rows * a.parts)), blk(256);
+  const dim3 grid((unsigned)(a.n_rows * a.parts));
   const dim3 gfin((unsigned)((a.n_rows + 3) / 4));
+  // Without room for partials a row is one block: of 16 wavefronts instead of 4
+  // while two such blocks per CU hold every row and each thread still gets a
+  // few groups (21 rows of 151936, T = 0.7: 45 against 104 us; from 513 rows on the blocks of 4
+  // wavefronts fill the card and their ends overlap).
+  const bool wide = a.parts == 1 && a.n_rows <= kSampleWideRows && (a.vocab >> 2) >= kSampleWideGroups;
+  uint32_t tbits;
+  std::memcpy(&tbits, &a.temperature, 4);
+  const bool recip = a.temperature >= 9.5367432e-07f && a.temperature <= 1048576.0f &&   // 2^-20 .. 2^20
+                     (tbits & 0x7fffffu) != 0x7fffffu;
+  a.inv_temperature = 1.0f / a.temperature;
+  auto go_t = [&](auto BF, auto ST, auto TS) {
+    constexpr bool bf = decltype(BF)::value, sf = decltype(ST)::value;
+    constexpr int ts = decltype(TS)::value;
+    if (wide) hipLaunchKernelGGL((sample_kernel<bf, sf, 1024, ts>), grid, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL((sample_kernel<bf, sf, 256, ts>), grid, dim3(256), 0, st, a);
+  };
+  auto go = [&](auto BF, auto ST) {
+    constexpr bool bf = decltype(BF)::value, sf = decltype(ST)::value;
+    if (a.temperature == 1.0f) go_t(BF, ST, std::integral_constant<int, T_ONE>{});
+    else if (recip) go_t(BF, ST, std::integral_constant<int, T_RECIP>{});
+    else go_t(BF, ST, std::integral_constant<int, T_FULL>{});
+    if (a.parts > 1) hipLaunchKernelGGL((sample_finalize_kernel<bf, sf>), gfin, dim3(256), 0, st, a);
+  };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
   if (a.bf16) {
-    if (stateful) hipLaunchKernelGGL((sample_kernel<true, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((sample_kernel<true, false>), grid, blk, 0, st, a);
-    if (a.parts > 1) {
-      if (stateful) hipLaunchKernelGGL((sample_finalize_kernel<true, true>), gfin, blk, 0, st, a);
-      else hipLaunchKernelGGL((sample_finalize_kernel<true, false>), gfin, blk, 0, st, a);
-    }
+    if (stateful) go(yes, yes);
+    else go(yes, no);
   } else {
-    if (stateful) hipLaunchKernelGGL((sample_kernel<false, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((sample_kernel<false, false>), grid, blk, 0, st, a);
-    if (a.parts > 1) {
-      if (stateful) hipLaunchKernelGGL((sample_finalize_kernel<false, true>), gfin, blk, 0, st, a);
-      else hipLaunchKernelGGL((sample_finalize_kernel<false, false>), gfin, blk, 0, st, a);
-    }
+    if (stateful) go(no, yes);
+    else go(no, no);
   }
   return hipGetLastError();
 }

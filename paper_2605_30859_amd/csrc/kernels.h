@@ -140,6 +140,7 @@ hipError_t launch_attention_shared(const void* q, const void* k_pool, const void
 // ---- sampler (k_sample.hip)
 struct SampleArgs {
   const void* logits; int n_rows; int vocab; bool bf16; uint64_t seed; float temperature;
+  float inv_temperature;      // set by the launcher
   const int32_t* row_logit;   // row r reads logits row row_logit[r], else traj[r] / logit_div, else r
   int logit_div;
   const int32_t* traj;        // [n_rows] trajectory id (counter word 1 is traj + traj_base)
@@ -166,6 +167,9 @@ struct SamplePart {
 // kSampleMinGroups groups of 4 logits, at most kSampleMaxParts per row, so
 // n_rows * parts <= kSampleBlocks + n_rows
 constexpr int kSampleBlocks = 1024, kSampleMinGroups = 512, kSampleMaxParts = 128;
+// rows in one block each: blocks of 16 wavefronts up to so many rows, from so
+// many groups of 4 logits
+constexpr int kSampleWideRows = 512, kSampleWideGroups = 4096;
 int sample_parts(int n_rows, int vocab);
 hipError_t launch_sample(const SampleArgs& a, hipStream_t st);
 hipError_t launch_gumbel_map(const float* u, float* g, int64_t n, bool fast, hipStream_t st);

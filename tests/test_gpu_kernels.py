@@ -11,7 +11,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from oracle.fp32math import gumbel_f32
-from oracle.sampler import sample_row
+from oracle.sampler import sample_row, sample_token
 from oracle.selection import group_decision, reclaimed_pages, LIVE, EOS, TRUNC, ABORTED
 from oracle import sweep as OS
 from workload import sweep_attention_inputs, sweep_sampler_logits, sweep_selection_inputs
@@ -225,6 +225,39 @@ def test_sampler_small(dtype, rows, vocab, temp):
         assert tok[r] == taken, (r, tok[r], taken)
         assert abs(lp[r] - slp) < 1e-4, (r, lp[r], slp)
         assert abs(ent[r] - sent) < 1e-4, (r, ent[r], sent)
+
+
+@pytest.mark.parametrize("rows,vocab", [(7, 4), (5, 1028), (3, 4096 * 4 - 4), (3, 4096 * 4), (513, 4096 * 4), (2, 40000)])
+@pytest.mark.parametrize("temp", [1.0, 0.7, 1.9999999, 1e-7])
+def test_sampler_threshold_edges(rows, vocab, temp):
+    """Tokens bit-exact where the scan's threshold could go wrong: logits that
+    dwarf or drown the noise, mostly masked rows, an infinite logit, rising and
+    falling rows, one lone winner; one block of 4 or of 16 wavefronts per row;
+    temperatures by reciprocal (0.7) and by division (significand of all ones;
+    below 2^-20)."""
+    B = _b()
+    say(f"sampler threshold rows={rows} V={vocab} T={temp}")
+    rng = np.random.default_rng([rows, vocab])
+    z = (rng.standard_normal((rows, vocab)) * 3.0).astype(np.float32)
+    kinds = min(rows, 7)
+    for r in range(rows):
+        k = r % 7
+        if k == 1: z[r] *= 1e4
+        elif k == 2: z[r] *= 1e-5
+        elif k == 3: z[r][rng.random(vocab) < 0.97] = -np.inf; z[r, vocab // 2] = 0.0
+        elif k == 4: z[r] = np.sort(z[r])
+        elif k == 5: z[r] = np.sort(z[r])[::-1]
+        elif k == 6: z[r, vocab - 1] = np.inf; z[r, vocab - 3] = np.inf
+    step = np.arange(rows, dtype=np.int32) + 3
+    traj = np.arange(rows, dtype=np.int32) * 5 + 1
+    out = [torch.zeros(rows, dtype=d, device=DEV) for d in (torch.int32, torch.float32, torch.float32)]
+    B.darts_sample(torch.from_numpy(z).to(DEV), B.DARTS_F32, 77, torch.from_numpy(traj).to(DEV),
+                   torch.from_numpy(step).to(DEV), temp, None, *out)
+    tok = out[0].cpu().numpy()
+    with np.errstate(over="ignore"):
+        for r in list(range(kinds)) + ([rows - 1] if rows > kinds else []):
+            exp = sample_token(z[r], np.float32(temp), int(traj[r]), int(step[r]), 77)
+            assert tok[r] == exp, (rows, vocab, temp, r, int(tok[r]), exp)
 
 
 def test_sampler_full_sweep_size():

@@ -438,8 +438,7 @@ size_t darts_attn_workspace_bytes(int32_t n_rows, int32_t n_q_heads, int32_t n_k
  *                 rows with ctx <= 0 are left unwritten), or NULL: every row
  *                 has max_ctx keys.  This equal-context form is the one a
  *                 decode step takes (in bf16 the work is mapped without a
- *                 device-built list, and from 64 rows each wavefront keeps
- *                 two page pairs in flight).
+ *                 device-built list).
  *   d_workspace   darts_attn_workspace_bytes(...) bytes, 256-byte aligned
  * In bf16 the value slots of a row's last page at or past ctx_len[r] take
  * part in the P.V product with weight 0, so they must hold finite values

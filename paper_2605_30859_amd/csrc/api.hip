@@ -739,7 +739,7 @@ static int run_attention(darts_ctx* c, int layer, int n_rows, const int32_t* row
   }
   HIPCHK(c, launch_attention(c->q, kp, vp, c->n_pages, c->page_table, c->max_pages, row_pt, nullptr,
                              ctx_mod, ctx_base, n_rows, c->hq, c->hkv, c->hd, max_ctx, c->bf16,
-                             c->attn, c->attn_ws, c->attn_ws_bytes, c->st, e0, e1));
+                             c->attn, c->attn_ws, c->attn_ws_bytes, c->st, e0, e1, c->pp));
   return DARTS_OK;
 }
 

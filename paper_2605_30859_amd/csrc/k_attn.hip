@@ -38,6 +38,8 @@ struct CtxSpec {
   int skip;                // keys [0, skip) are attended by the shared-prefix kernel (a
                            // multiple of 16; 0 when prefixes are not shared)
   int pt_rows;             // row_pt values are clamped into [0, pt_rows) when > 0
+  int nt_from;             // pages from this index of a row's list on are the row's alone: their
+                           // loads are non-temporal
 };
 __device__ __forceinline__ int pt_row(const CtxSpec& c, int r) {
   if (!c.row_pt) return r;
@@ -169,14 +171,19 @@ constexpr int kPst = 40;   // P row stride in LDS (bf16): 80 bytes
 // K is read token-major straight into the MFMA B operand (16 B per lane, one
 // contiguous 1 KB block of the page per 32-wide K step);
 // V pages store 8 consecutive tokens of one dim contiguously, so the P.V
-// B operand is also one 16 B load per lane.  Page ids of the next pair are
-// fetched one iteration ahead so that the page-id -> key/value load chain is
-// not serial.  With DB the loads of the next pair are issued before the
-// current pair is computed (two pairs in flight; the 128-dim kernel then
-// needs all 256 registers a wavefront may hold at two per SIMD): faster with
-// many rows (5-8% from 64 live rows up), slower with few.
-template <int HD, bool DB>
-__device__ __forceinline__ void attn_page_loop(const bf16x8_t (&qa)[HD / 32], const bf16_t* kpool,
+// B operand is also one 16 B load per lane.  The page-id -> key/value load chain is
+// not serial: a wavefront holds the ids of 64 pages, one per lane, and those of
+// the next 64.  One pair is in flight per wavefront; two (245 registers) were no
+// faster once a wavefront's page ids and addresses are scalar and its own
+// pages' loads non-temporal.
+// NT: non-temporal loads.
+template <bool NT>
+__device__ __forceinline__ bf16x8_t load_frag(const bf16_t* p) {
+  if constexpr (NT) return __builtin_bit_cast(bf16x8_t, __builtin_nontemporal_load((const u32x4_t*)p));
+  else return __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)p);
+}
+template <int HD, bool NT>
+__device__ __forceinline__ void attn_page_run(const bf16x8_t (&qa)[HD / 32], const bf16_t* kpool,
                                                const bf16_t* vpool, const CtxSpec& cs,
                                                const int32_t* pt, int pbeg, int pend, int ctx,
                                                int kvh, int hkv, bf16_t* P, AttnAcc<HD>& acc) {
@@ -192,14 +199,14 @@ __device__ __forceinline__ void attn_page_loop(const bf16x8_t (&qa)[HD / 32], co
     const bf16_t* kpb = kpool + k_off(pb, kvh, col, quad * 8, hkv, HD);
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) {
-      F.ka[kk] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(kpa + kk * kPage * 32));
-      F.kb[kk] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(kpb + kk * kPage * 32));
+      F.ka[kk] = load_frag<NT>(kpa + kk * kPage * 32);
+      F.kb[kk] = load_frag<NT>(kpb + kk * kPage * 32);
     }
     const int vpage = quad < 2 ? pa : pb;
     const bf16_t* vb = vpool + v_off(vpage, kvh, (quad & 1) * 8, col, hkv, HD);
 #pragma unroll
     for (int nb = 0; nb < NNB; ++nb)
-      F.vv[nb] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(vb + nb * 16 * 8));
+      F.vv[nb] = load_frag<NT>(vb + nb * 16 * 8);
   };
   auto compute = [&](int p, const PagePair<HD>& F) {
     f32x4_t sa = {0.f, 0.f, 0.f, 0.f}, sb = {0.f, 0.f, 0.f, 0.f};
@@ -245,44 +252,29 @@ __device__ __forceinline__ void attn_page_loop(const bf16x8_t (&qa)[HD / 32], co
       acc.O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa8, F.vv[nb], acc.O[nb], 0, 0, 0);
     __builtin_amdgcn_wave_barrier();   // P is rewritten by the next pair
   };
-  if constexpr (DB) {
-    auto ids = [&](int p, int& a, int& b) {
-      a = pt[p];
-      b = p + 1 < pend ? pt[p + 1] : a;
-    };
-    if (pbeg >= pend) return;
-    PagePair<HD> F0, F1;
-    int ia, ib;
-    ids(pbeg, ia, ib);
-    load(pbeg, F0, ia, ib);
-    if (pbeg + 2 < pend) ids(pbeg + 2, ia, ib);
-    for (int p = pbeg; p < pend; p += 4) {
-      if (p + 2 < pend) {
-        load(p + 2, F1, ia, ib);
-        if (p + 4 < pend) ids(p + 4, ia, ib);
-      }
-      compute(p, F0);
-      if (p + 2 >= pend) break;
-      if (p + 4 < pend) {
-        load(p + 4, F0, ia, ib);
-        if (p + 6 < pend) ids(p + 6, ia, ib);
-      }
-      compute(p + 2, F1);
+  PagePair<HD> F;
+  // lane i: the id of page i of this run of 64 pages, and of the next run
+  int ids = pt[min(pbeg + lane, pend - 1)], next_ids = ids;
+  for (int p = pbeg; p < pend; p += 2) {
+    const int i = (p - pbeg) & 63;
+    if (i == 0) {
+      if (p > pbeg) ids = next_ids;
+      if (p + 64 < pend) next_ids = pt[min(p + 64 + lane, pend - 1)];
     }
-  } else {
-    PagePair<HD> F;
-    int nxa = pbeg < pend ? pt[pbeg] : 0;
-    int nxb = pbeg + 1 < pend ? pt[pbeg + 1] : nxa;
-    for (int p = pbeg; p < pend; p += 2) {
-      const int ca = nxa, cb = nxb;
-      if (p + 2 < pend) {
-        nxa = pt[p + 2];
-        nxb = p + 3 < pend ? pt[p + 3] : nxa;
-      }
-      load(p, F, ca, cb);
-      compute(p, F);
-    }
+    load(p, F, __builtin_amdgcn_readlane(ids, i), __builtin_amdgcn_readlane(ids, i + 1));
+    compute(p, F);
   }
+}
+
+// The pages other rows share, whose re-reads hit the caches, then the row's own.
+template <int HD>
+__device__ __forceinline__ void attn_page_loop(const bf16x8_t (&qa)[HD / 32], const bf16_t* kpool,
+                                               const bf16_t* vpool, const CtxSpec& cs, int nt_from,
+                                               const int32_t* pt, int pbeg, int pend, int ctx,
+                                               int kvh, int hkv, bf16_t* P, AttnAcc<HD>& acc) {
+  const int mid = min(max(nt_from, pbeg), pend);
+  if (pbeg < mid) attn_page_run<HD, false>(qa, kpool, vpool, cs, pt, pbeg, mid, ctx, kvh, hkv, P, acc);
+  if (mid < pend) attn_page_run<HD, true>(qa, kpool, vpool, cs, pt, mid, pend, ctx, kvh, hkv, P, acc);
 }
 
 // sum of a lane-partial over the 16 lanes of a query row
@@ -301,11 +293,19 @@ __device__ __forceinline__ float row16_sum(float l) {
 // whose keys span several chunks writes unnormalised partials (o, max, sum)
 // and the combine kernel merges them.  With a shared prefix the row's keys
 // start at cs.skip and chunk 0 starts from the prefix partials.
-template <int HD, bool DB>
-__device__ __forceinline__ void attn_bf16_body(const AttnBf16Args& A) {
+//
+// Bound by HBM.  With uniform page ids and addresses (149 registers, 192 before)
+// and non-temporal loads of unshared pages: 777 rows x 1123 keys, 32/4 heads x
+// 128: 300 us (6.0 TB/s), before 378; 1024 ragged rows, 32/8 heads: 1700 us,
+// before 1800; 512 rows of which 16 at a time share 32 of 57 pages: 196 us,
+// before 211.  Equal contiguous shares of all page pairs per wavefront, whatever
+// the rows, were no faster: cut rows cost more to merge than an uneven last
+// round loses.
+template <int HD>
+__global__ void __launch_bounds__(256) attn_bf16_kernel(AttnBf16Args A) {
   constexpr int NKK = HD / 32, NNB = HD / 16;
   __shared__ __attribute__((aligned(16))) bf16_t plds[4][16 * kPst];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hq = A.hq, hkv = A.hkv;
   const int G = hq / hkv;
   const int quad = lane >> 4, col = lane & 15;
@@ -327,6 +327,14 @@ __device__ __forceinline__ void attn_bf16_body(const AttnBf16Args& A) {
     const int nch = (npg - skip_pages + A.chunk_pages - 1) / A.chunk_pages;
     const int pbeg = skip_pages + chunk * A.chunk_pages;
     const int pend = min(pbeg + A.chunk_pages, npg);
+    int nt_from = A.cs.nt_from;
+    if (nt_from < 0 && pbeg < pend) {
+      // not told: a chunk whose first page a neighbouring row lists at the same
+      // place is taken to be shared (only the loads' cache policy depends on it)
+      const int id = pt[pbeg];
+      const int up = row > 0 ? pt[pbeg - A.pt_stride] : -1, down = row + 1 < A.n_rows ? pt[pbeg + A.pt_stride] : -1;
+      nt_from = __builtin_amdgcn_readfirstlane(id == up || id == down) ? pend : pbeg;
+    }
 
     bf16x8_t qa[NKK];
     {
@@ -364,7 +372,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnBf16Args& A) {
         acc.l[i] = col == 0 ? L : 0.f;
       }
     }
-    attn_page_loop<HD, DB>(qa, A.kpool, A.vpool, A.cs, pt, pbeg, pend, ctx, kvh, hkv, P, acc);
+    attn_page_loop<HD>(qa, A.kpool, A.vpool, A.cs, nt_from, pt, pbeg, pend, ctx, kvh, hkv, P, acc);
 
     float lrow[4];
 #pragma unroll
@@ -394,18 +402,6 @@ __device__ __forceinline__ void attn_bf16_body(const AttnBf16Args& A) {
       if (col == 0) A.ws_ml[(int64_t)cid * hq + qh] = make_float2(acc.m[i], lrow[i]);
     }
   }
-}
-
-// Entry points: one page pair in flight per wavefront (registers as the code
-// needs them), or two (double-buffered), held to two wavefronts per SIMD,
-// i.e. at most 256 registers.
-template <int HD>
-__global__ void __launch_bounds__(256) attn_bf16_kernel(AttnBf16Args A) {
-  attn_bf16_body<HD, false>(A);
-}
-template <int HD>
-__global__ void __launch_bounds__(256, 2) attn_bf16_db_kernel(AttnBf16Args A) {
-  attn_bf16_body<HD, true>(A);
 }
 
 // Shared-prefix attention.  The members of a prompt group (consecutive rows
@@ -452,7 +448,7 @@ __global__ void __launch_bounds__(256) attn_prefix_kernel(AttnPrefixArgs A) {
     for (int i = 0; i < 4; ++i) { acc.m[i] = -INFINITY; acc.l[i] = 0.f; }
 #pragma unroll
     for (int nb = 0; nb < NNB; ++nb) acc.O[nb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    attn_page_loop<HD, false>(qa, A.kpool, A.vpool, A.cs, pt, pbeg, pend, ctx, kvh, hkv, P, acc);
+    attn_page_run<HD, false>(qa, A.kpool, A.vpool, A.cs, pt, pbeg, pend, ctx, kvh, hkv, P, acc);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float l = row16_sum(acc.l[i]);
@@ -839,14 +835,13 @@ static int attn_slots(int hd) {
 // took 1.85 / 1.76 / 1.72 / 1.82 ms: fewer chunks mean fewer partial sums and
 // less per-item work, more mean better balance).  Equal contexts: the
 // chunk count that minimises the kernel's makespan, rounds of resident
-// wavefronts times pages per chunk (plus a page of fixed work per item), plus
+// wavefronts times pages per chunk (plus a page of fixed work per item), where a
+// last round after full ones counts for as much as it fills, at least half (777
+// rows x 4 kv heads in whole rows: 300 us; in 3 chunks, which whole rounds
+// favour: 346), plus
 // the partial-sum round trip and combine launch when rows are split; at most
 // ~4 rounds of items and chunks of at least 4 pages.
 constexpr int kRaggedChunkPages = 128;
-// equal-context launches with at least this many rows keep two page pairs in
-// flight per wavefront (measured on the Qwen3-8B-shaped rollout: 4-8% faster
-// from 64 live rows up, 3-5% slower below)
-constexpr int kAttnDbMinRows = 64;
 static int choose_chunk_pages(int n_rows, int hkv, int max_ctx, bool uniform, int hd) {
   const int64_t units = (int64_t)n_rows * hkv;
   const int npg = (max_ctx + kPage - 1) / kPage;
@@ -861,8 +856,10 @@ static int choose_chunk_pages(int n_rows, int hkv, int max_ctx, bool uniform, in
     if (nch != n) continue;                 // same split as a smaller n
     if (n > 1 && c < 4) break;              // chunks of at least 4 pages (64 keys)
     const double items = (double)units * nch;
-    const double rounds = std::ceil(items / slots);
-    double t = rounds * (c + 1.0);
+    // a last round that is not full has the memory to itself: its wavefronts
+    // run up to about twice as fast
+    const double full = std::floor(items / slots), rest = items / slots - full;
+    double t = (full + (rest <= 0.0 ? 0.0 : full < 1.0 ? 1.0 : std::max(rest, 0.5))) * (c + 1.0);
     if (nch > 1) t += 0.5 * items / slots + 3.0;
     if (t < best) { best = t; best_c = c; }
   }
@@ -964,18 +961,9 @@ hipError_t launch_attention_spec(const void* q, const void* k_pool, const void* 
     a.ws_o = w.ws_o; a.ws_ml = w.ws_ml; a.out = (bf16_t*)out;
     a.pre_o = nullptr; a.pre_ml = nullptr; a.pre_nch = 0;
     if (ev0) (void)hipEventRecord(ev0, st);
-    // two page pairs in flight for decode batches of 64 rows or more
-    const bool db = uniform && n_rows >= kAttnDbMinRows;
-    if (hd == 128) {
-      if (db) hipLaunchKernelGGL(attn_bf16_db_kernel<128>, grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(attn_bf16_kernel<128>, grid, dim3(256), 0, st, a);
-    } else if (hd == 64) {
-      if (db) hipLaunchKernelGGL(attn_bf16_db_kernel<64>, grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(attn_bf16_kernel<64>, grid, dim3(256), 0, st, a);
-    } else if (hd == 32) {
-      if (db) hipLaunchKernelGGL(attn_bf16_db_kernel<32>, grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(attn_bf16_kernel<32>, grid, dim3(256), 0, st, a);
-    }
+    if (hd == 128) hipLaunchKernelGGL(attn_bf16_kernel<128>, grid, dim3(256), 0, st, a);
+    else if (hd == 64) hipLaunchKernelGGL(attn_bf16_kernel<64>, grid, dim3(256), 0, st, a);
+    else if (hd == 32) hipLaunchKernelGGL(attn_bf16_kernel<32>, grid, dim3(256), 0, st, a);
     else return hipErrorInvalidValue;
     if (ev1) (void)hipEventRecord(ev1, st);
     hipError_t e = hipGetLastError();
@@ -1028,6 +1016,7 @@ hipError_t launch_attention_shared(const void* q, const void* k_pool, const void
   CtxSpec cs;
   cs.ctx_len = nullptr; cs.mod = 0; cs.base = ctx; cs.row_pt = row_traj; cs.max_ctx = ctx;
   cs.n_pages = n_pages; cs.skip = prefix_pages * kPage; cs.pt_rows = pt_rows;
+  cs.nt_from = prefix_pages;
   if (build_groups)
     hipLaunchKernelGGL(attn_groups_kernel, dim3(1), dim3(1024), 0, st, row_traj, n_rows, m, w.grp_row0,
                        w.grp_n, w.n_groups, n_groups_out);
@@ -1077,8 +1066,16 @@ hipError_t launch_attention(const void* q, const void* k_pool, const void* v_poo
                             const int32_t* row_pt, const int32_t* ctx_len, int ctx_mod,
                             int ctx_base, int n_rows, int hq, int hkv, int hd, int max_ctx,
                             bool bf16, void* out, void* ws, size_t ws_bytes, hipStream_t st,
-                            hipEvent_t ev0, hipEvent_t ev1) {
+                            hipEvent_t ev0, hipEvent_t ev1, int shared_pages) {
   CtxSpec cs;
+  // Non-temporal loads of what no other row reads (streams run at 7.0 TB/s with
+  // them, at 6.3 without): in a rollout the pages after the prompt's, since the
+  // other layers pass through the caches before a layer is read again.  A
+  // stateless call's rows may share pages, which the kernel looks at, and below
+  // the size of the Infinity Cache a caller that comes back with the same pools
+  // finds them there (6 rows of 6000 keys: 25.9 us, non-temporal 28.0).
+  const double kv_bytes = 4.0 * n_rows * hkv * hd * max_ctx;
+  cs.nt_from = row_pt ? shared_pages : kv_bytes >= 256e6 ? -1 : INT32_MAX;
   cs.ctx_len = ctx_len; cs.mod = ctx_mod; cs.base = ctx_base; cs.row_pt = row_pt;
   cs.max_ctx = max_ctx; cs.n_pages = n_pages; cs.skip = 0; cs.pt_rows = 0;
   return launch_attention_spec(q, k_pool, v_pool, page_table, pt_stride, cs, n_rows, hq, hkv, hd,

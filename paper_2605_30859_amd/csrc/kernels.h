@@ -108,13 +108,15 @@ hipError_t launch_pack_strips(void* W, int64_t rows, int K, hipStream_t st);
 
 // ---- attention (k_attn.hip)
 size_t attn_workspace_bytes(int n_rows, int hq, int hkv, int hd, int max_ctx);
-// ctx(r) = ctx_len ? ctx_len[r] : (ctx_mod ? r % ctx_mod : 0) + ctx_base
+// ctx(r) = ctx_len ? ctx_len[r] : (ctx_mod ? r % ctx_mod : 0) + ctx_base.
+// shared_pages: that many pages at the front of a row's list are other rows' too
+// (their loads stay in the caches, the rest is loaded non-temporal).
 hipError_t launch_attention(const void* q, const void* k_pool, const void* v_pool,
                             int64_t n_pages, const int32_t* page_table, int pt_stride,
                             const int32_t* row_pt, const int32_t* ctx_len, int ctx_mod,
                             int ctx_base, int n_rows, int hq, int hkv, int hd, int max_ctx,
                             bool bf16, void* out, void* ws, size_t ws_bytes, hipStream_t st,
-                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int shared_pages = 0);
 // Causal attention of n_prompts prompts of len positions (a multiple of 16),
 // bf16: row i*len + t of q and out is position t of prompt i, whose pages are
 // the first len/16 entries of page_table + i * pt_step.

@@ -134,3 +134,37 @@ def test_gemm_large_tiles_every_row(M, N, K, epi):
     tol = 2 ** -8 * ref.abs() + 1e-3 if epi in (1, 3) else K * 2.0 ** -24 * (ref.abs() + 1.0)
     assert bool((err <= tol).all()), (M, N, K, epi, float((err - tol).max()))
     assert bool((out[M:] == 7.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(1, 5, 1, 0), (17, 33, 7, 0), (16, 16, 130, 2), (33, 48, 516, 2), (2, 64, 20, 3),
+                                       (35, 96, 1027, 3), (64, 1024, 128, 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gemm_f32_any_size(M, N, K, epi, shift):
+    """fp32 operands: tile remainders, K shorter and longer than the wavefronts'
+    share, K and addresses that are not multiples of four (shift: A starts 4
+    bytes off).  Against float64; tolerance K*2^-24 relative to the sum of
+    magnitudes (the bound for a sum of K rounded products in any order), and
+    four ulp more for the SwiGLU function."""
+    print(f"gemm f32 M={M} N={N} K={K} epi={epi} shift={shift}", flush=True)
+    B = _b()
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    buf = torch.randn(M * K + 1, device=DEV, generator=g)
+    a = buf[shift:shift + M * K].view(M, K)
+    w = torch.randn(N, K, device=DEV, generator=g)
+    cols = N // 2 if epi == 3 else N
+    out = torch.full((M + 16, cols), 3.0, device=DEV)
+    B.darts_gemm(a, w, out, M, N, K, B.DARTS_F32, epi)
+    torch.cuda.synchronize()
+    ref, mag = a.double() @ w.double().T, a.double().abs() @ w.double().abs().T
+    tol = (K + 2) * 2.0 ** -24 * mag
+    if epi == 3:
+        ref, tol = ref.view(M, N // 32, 2, 16), tol.view(M, N // 32, 2, 16)
+        sg = torch.nn.functional.silu(ref[:, :, 0])
+        # |silu'| <= 1.1
+        tol = (1.1 * tol[:, :, 0] + 2.0 ** -21 * sg.abs()) * ref[:, :, 1].abs() + sg.abs() * tol[:, :, 1] + 1e-6
+        ref, tol = (sg * ref[:, :, 1]).reshape(M, cols), tol.reshape(M, cols)
+    elif epi == 2:
+        ref, tol = ref + 3.0, tol + 2.0 ** -22 * (ref.abs() + 3.0)
+    err = (out[:M].double() - ref).abs()
+    assert bool((err <= tol).all()), float((err - tol).max())
+    assert bool((out[M:] == 3.0).all())

@@ -64,7 +64,8 @@ struct darts_ctx {
   int32_t* m_topk_id = nullptr;
   float* m_topk_w = nullptr;
   int32_t* m_pos_of = nullptr;
-  int32_t* m_cnt = nullptr;       // counts | offsets | cursors, E each
+  int32_t* m_cnt = nullptr;       // counts | offsets, E each
+  int32_t* m_blk = nullptr;       // [kMoeBlocks][E] counts, then first slots, per block
   int32_t* m_row_of = nullptr;    // [pairs] input row of each expert-sorted position
   void* m_h_perm = nullptr;
   void* m_y_perm = nullptr;
@@ -559,7 +560,8 @@ int darts_init(const darts_model_cfg* model, int32_t m, int32_t k, const darts_r
     A(&c->m_topk_id, pairs * 4);
     A(&c->m_topk_w, pairs * 4);
     A(&c->m_pos_of, pairs * 4);
-    A(&c->m_cnt, (size_t)3 * c->E * 4);
+    A(&c->m_cnt, (size_t)2 * c->E * 4);
+    A(&c->m_blk, (size_t)kMoeBlocks * c->E * 4);
     A(&c->m_logits, (size_t)rows_max * c->Epad * 4);
     A(&c->m_mtiles, (pairs / kGroupedTileRowsMin + c->E + 1) * 4);
     A(&c->m_mtiles_dn, (pairs / kGroupedTileRowsMin + c->E + 1) * 4);
@@ -816,7 +818,7 @@ static int run_layers(darts_ctx* c, int n, const int32_t* row_pt, const int32_t*
       m.gemm_ws_bytes = c->gemm_ws_bytes;
       m.w_down = (const bf16_t*)w.wedown; m.topk_id = c->m_topk_id; m.topk_w = c->m_topk_w;
       m.pos_of = c->m_pos_of; m.counts = c->m_cnt; m.offsets = c->m_cnt + c->E;
-      m.cursors = c->m_cnt + 2 * c->E;
+      m.blk = c->m_blk;
       m.h_perm = (bf16_t*)c->m_h_perm; m.y_perm = (bf16_t*)c->m_y_perm;
       const int64_t dstride = (int64_t)c->nl * c->topk;
       m.route_key = row_key; m.dbg_stride = dstride;

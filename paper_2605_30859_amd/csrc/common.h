@@ -111,6 +111,35 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Exclusive scan of one int per thread over a 1024-thread block: inclusive
+// scans inside each wavefront (shuffles), the 16 wavefront totals scanned by
+// the first wavefront through LDS, then added back.  sh holds >= 16 ints.
+__device__ __forceinline__ int block_excl_scan1024(int v, int32_t* sh, int* total) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += x;
+  }
+  if (lane == 63) sh[w] = incl;
+  __syncthreads();
+  if (w == 0) {
+    int t = lane < 16 ? sh[lane] : 0;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const int x = __shfl_up(t, o, 64);
+      if (lane >= o) t += x;
+    }
+    if (lane < 16) sh[16 + lane] = t;    // inclusive totals of wavefronts 0..lane
+  }
+  __syncthreads();
+  const int before = w > 0 ? sh[16 + w - 1] : 0;
+  *total = sh[16 + 15];
+  __syncthreads();                      // sh may be reused by the next scan
+  return before + incl - v;
+}
+
 }  // namespace darts
 
 namespace darts {

@@ -4,7 +4,7 @@
 //             zero-padded to a multiple of 128); per row r = softmax over the E
 //             logits, the k largest (ties to the lower expert id), weights
 //             renormalised over the k
-//   offsets:  per-expert counts (block histogram), their exclusive scan, one
+//   offsets:  per-expert counts (block histograms), their exclusive scan, one
 //             list of expert row tiles per projection, and a position in its
 //             expert's segment for every (row, slot) pair
 //   experts:  grouped GEMMs over the expert segments: gate/up (+ SwiGLU
@@ -157,54 +157,61 @@ __global__ void __launch_bounds__(256) moe_topk_kernel(const float* __restrict__
   }
 }
 
-// Exclusive scan of one int per thread over a 1024-thread block: inclusive
-// scans inside each wavefront (shuffles), the 16 wavefront totals scanned by
-// the first wavefront through LDS, then added back.  sh holds >= 16 ints.
-__device__ __forceinline__ int block_excl_scan1024(int v, int32_t* sh, int* total) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int x = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += x;
+// Lists of a routing: per-expert counts and their exclusive scan, and the
+// non-empty expert row tiles (e << 16 | tile) of either projection.
+struct MoeLists {
+  int32_t *counts, *offsets, *mtiles, *n_mtiles, *mtiles2, *n_mtiles2, *touched_out;
+  int tile_rows, tile_rows2;
+};
+// The lists from thread e's count v of expert e (0 for e >= E), by one block of
+// 1024 threads; returns the expert's offset.
+__device__ __forceinline__ int moe_lists(const MoeLists& l, int v, int E, int32_t* sh) {
+  const int tid = threadIdx.x;
+  int total;
+  const int ex = block_excl_scan1024(v, sh, &total);
+  const int nt = (v + l.tile_rows - 1) / l.tile_rows;
+  int ntiles;
+  const int tex = block_excl_scan1024(nt, sh, &ntiles);
+  if (tid < E) {
+    l.counts[tid] = v;
+    l.offsets[tid] = ex;
+    for (int j = 0; j < nt; ++j) l.mtiles[tex + j] = (tid << 16) | j;
   }
-  if (lane == 63) sh[w] = incl;
-  __syncthreads();
-  if (w == 0) {
-    int t = lane < 16 ? sh[lane] : 0;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const int x = __shfl_up(t, o, 64);
-      if (lane >= o) t += x;
-    }
-    if (lane < 16) sh[16 + lane] = t;    // inclusive totals of wavefronts 0..lane
+  if (tid == 0) *l.n_mtiles = ntiles;
+  // the second list (another row tile for the other projection)
+  const int nt2 = (v + l.tile_rows2 - 1) / l.tile_rows2;
+  int ntiles2;
+  const int tex2 = block_excl_scan1024(nt2, sh, &ntiles2);
+  if (tid < E)
+    for (int j = 0; j < nt2; ++j) l.mtiles2[tex2 + j] = (tid << 16) | j;
+  if (tid == 0) *l.n_mtiles2 = ntiles2;
+  if (l.touched_out) {
+    const int nz = __syncthreads_count(v > 0);
+    if (tid == 0) *l.touched_out = nz;
   }
-  __syncthreads();
-  const int before = w > 0 ? sh[16 + w - 1] : 0;
-  *total = sh[16 + 15];
-  __syncthreads();                      // sh may be reused by the next scan
-  return before + incl - v;
+  return ex;
+}
+// Positions of pairs [beg, end): pair i (row i / k) takes the next free slot of
+// its expert's segment (cursor[e], in LDS), pos_of and its inverse row_of.
+__device__ __forceinline__ void moe_place(const int32_t* __restrict__ topk_id, int beg, int end, int E, int k,
+                                          int32_t* cursor, int32_t* __restrict__ pos_of,
+                                          int32_t* __restrict__ row_of) {
+  for (int i = beg + (int)threadIdx.x; i < end; i += 1024) {
+    const int e = topk_id[i];
+    if (e < 0 || e >= E) continue;
+    const int p = atomicAdd(&cursor[e], 1);
+    pos_of[i] = p;
+    row_of[p] = i / k;
+  }
 }
 
-// Single block: per-expert counts of the n_pairs routed (row, slot) pairs
-// (LDS histogram), their exclusive scan into offsets, cursors reset to 0, the
-// list of non-empty expert row tiles (e << 16 | tile) for the grouped GEMMs,
-// and every pair's position (pos_of) with its inverse (row_of).
-__global__ void __launch_bounds__(1024) moe_offsets_kernel(const int32_t* __restrict__ topk_id,
-                                                           int n_pairs, int E, int k,
-                                                           int32_t* __restrict__ counts,
-                                                           int32_t* __restrict__ offsets,
-                                                           int32_t* __restrict__ cursors,
-                                                           int32_t* __restrict__ mtiles,
-                                                           int32_t* __restrict__ n_mtiles,
-                                                           int32_t* __restrict__ mtiles2,
-                                                           int32_t* __restrict__ n_mtiles2,
-                                                           int32_t* __restrict__ pos_of,
-                                                           int32_t* __restrict__ row_of,
-                                                           int32_t* __restrict__ touched_out,
-                                                           int tile_rows, int tile_rows2) {
+// Decode batches: everything in a single block, counts by an LDS histogram of
+// the n_pairs routed (row, slot) pairs.
+__global__ void __launch_bounds__(1024) moe_offsets_kernel(const int32_t* __restrict__ topk_id, int n_pairs, int E,
+                                                           int k, MoeLists lists, int32_t* __restrict__ pos_of,
+                                                           int32_t* __restrict__ row_of) {
   __shared__ int32_t hist[1024];
-  __shared__ int32_t sh[1024];
+  __shared__ int32_t sh[32];
   const int tid = threadIdx.x;
   hist[tid] = 0;
   __syncthreads();
@@ -213,41 +220,58 @@ __global__ void __launch_bounds__(1024) moe_offsets_kernel(const int32_t* __rest
     if (e >= 0 && e < E) atomicAdd(&hist[e], 1);
   }
   __syncthreads();
-  const int v = tid < E ? hist[tid] : 0;
-  int total;
-  const int ex = block_excl_scan1024(v, sh, &total);
-  const int nt = (v + tile_rows - 1) / tile_rows;
-  int ntiles;
-  const int tex = block_excl_scan1024(nt, sh, &ntiles);
-  if (tid < E) {
-    counts[tid] = v;
-    offsets[tid] = ex;
-    cursors[tid] = 0;
-    for (int j = 0; j < nt; ++j) mtiles[tex + j] = (tid << 16) | j;
-  }
-  if (tid == 0) *n_mtiles = ntiles;
-  // the second list (another row tile for the other projection)
-  const int nt2 = (v + tile_rows2 - 1) / tile_rows2;
-  int ntiles2;
-  const int tex2 = block_excl_scan1024(nt2, sh, &ntiles2);
-  if (tid < E)
-    for (int j = 0; j < nt2; ++j) mtiles2[tex2 + j] = (tid << 16) | j;
-  if (tid == 0) *n_mtiles2 = ntiles2;
-  if (touched_out) {
-    const int nz = __syncthreads_count(v > 0);
-    if (tid == 0) *touched_out = nz;
-  }
-  // positions: pair i (row i / k) takes the next free slot of its expert's
-  // segment; hist becomes the per-expert cursor
-  hist[tid] = tid < E ? ex : 0;
+  const int ex = moe_lists(lists, tid < E ? hist[tid] : 0, E, sh);
+  hist[tid] = tid < E ? ex : 0;          // the per-expert cursors
   __syncthreads();
-  for (int i = tid; i < n_pairs; i += 1024) {
+  moe_place(topk_id, 0, n_pairs, E, k, hist, pos_of, row_of);
+}
+
+// Large batches (the prefill): the pairs go to kMoeBlocks blocks, which count
+// them (step 1) and place them (step 3); between the two one block turns the
+// blocks' counts into the lists and each block's first slot per expert.  A
+// prefill of 32768 rows x 8: 21 us in all, 228 us in a single block, whose LDS
+// atomics are the bound; up to kMoeOneBlockPairs pairs the single block takes
+// about as long as the three launches.
+constexpr int kMoeOneBlockPairs = 16384;
+__device__ __forceinline__ int moe_block_begin(int b, int n_pairs) { return (int)((int64_t)n_pairs * b / kMoeBlocks); }
+__global__ void __launch_bounds__(1024) moe_count_kernel(const int32_t* __restrict__ topk_id, int n_pairs, int E,
+                                                         int32_t* __restrict__ blk) {
+  __shared__ int32_t hist[1024];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  hist[tid] = 0;
+  __syncthreads();
+  const int end = moe_block_begin(b + 1, n_pairs);
+  for (int i = moe_block_begin(b, n_pairs) + tid; i < end; i += 1024) {
     const int e = topk_id[i];
-    if (e < 0 || e >= E) continue;
-    const int p = atomicAdd(&hist[e], 1);
-    pos_of[i] = p;
-    row_of[p] = i / k;
+    if (e >= 0 && e < E) atomicAdd(&hist[e], 1);
   }
+  __syncthreads();
+  if (tid < E) blk[b * E + tid] = hist[tid];
+}
+__global__ void __launch_bounds__(1024) moe_scan_kernel(int E, MoeLists lists, int32_t* __restrict__ blk) {
+  __shared__ int32_t sh[32];
+  const int tid = threadIdx.x;
+  int v = 0;
+  if (tid < E)
+#pragma unroll 16
+    for (int b = 0; b < kMoeBlocks; ++b) v += blk[b * E + tid];
+  int at = moe_lists(lists, v, E, sh);
+  if (tid < E)
+#pragma unroll 16
+    for (int b = 0; b < kMoeBlocks; ++b) {
+      const int n = blk[b * E + tid];
+      blk[b * E + tid] = at;
+      at += n;
+    }
+}
+__global__ void __launch_bounds__(1024) moe_place_kernel(const int32_t* __restrict__ topk_id, int n_pairs, int E,
+                                                         int k, const int32_t* __restrict__ blk,
+                                                         int32_t* __restrict__ pos_of, int32_t* __restrict__ row_of) {
+  __shared__ int32_t cursor[1024];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  cursor[tid] = tid < E ? blk[b * E + tid] : 0;
+  __syncthreads();
+  moe_place(topk_id, moe_block_begin(b, n_pairs), moe_block_begin(b + 1, n_pairs), E, k, cursor, pos_of, row_of);
 }
 
 // x[r] += sum_j w[r][j] * y[pos(r, j)]   (slot order, y in bf16, the sum in
@@ -373,9 +397,18 @@ hipError_t launch_moe_ffn(const MoeArgs& a, hipStream_t st, bool* normed) {
     DARTS_TOPK(kMoeMaxPerLane)
   }
 #undef DARTS_TOPK
-  hipLaunchKernelGGL(moe_offsets_kernel, dim3(1), dim3(1024), 0, st, a.topk_id, a.n_rows * a.k, a.E, a.k,
-                     a.counts, a.offsets, a.cursors, a.mtiles, a.n_mtiles, a.mtiles_dn, a.n_mtiles_dn,
-                     a.pos_of, a.row_of, a.touched_out, plan_gu.tile_rows, plan_dn.tile_rows);
+  const MoeLists lists{a.counts, a.offsets, a.mtiles, a.n_mtiles, a.mtiles_dn, a.n_mtiles_dn, a.touched_out,
+                       plan_gu.tile_rows, plan_dn.tile_rows};
+  const int n_pairs = a.n_rows * a.k;
+  if (n_pairs <= kMoeOneBlockPairs) {
+    hipLaunchKernelGGL(moe_offsets_kernel, dim3(1), dim3(1024), 0, st, a.topk_id, n_pairs, a.E, a.k, lists, a.pos_of,
+                       a.row_of);
+  } else {
+    hipLaunchKernelGGL(moe_count_kernel, dim3(kMoeBlocks), dim3(1024), 0, st, a.topk_id, n_pairs, a.E, a.blk);
+    hipLaunchKernelGGL(moe_scan_kernel, dim3(1), dim3(1024), 0, st, a.E, lists, a.blk);
+    hipLaunchKernelGGL(moe_place_kernel, dim3(kMoeBlocks), dim3(1024), 0, st, a.topk_id, n_pairs, a.E, a.k, a.blk,
+                       a.pos_of, a.row_of);
+  }
   const int Fe = a.Fe, d = a.d;
   // gate/up: N = 2*Fe, K = d (SwiGLU into h_perm), A rows gathered from xn;
   // down: N = d, K = Fe

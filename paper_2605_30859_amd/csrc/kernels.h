@@ -223,6 +223,7 @@ hipError_t launch_prefill_pages(int n_prompts, int m, const int32_t* grp_m, int 
                                 int32_t* refcnt, hipStream_t st);
 
 // ---- MoE FFN (k_moe.hip): x += sum over the top-k experts of w_e * expert_e(xn)
+constexpr int kMoeBlocks = 64;   // blocks that count and place the pairs of a large batch
 struct MoeArgs {
   bf16_t* xn;               // in: RMSNorm(x) (bf16); out: RMSNorm of the updated x when *normed
   float* x; int n_rows, d, E, k, Fe;
@@ -235,7 +236,8 @@ struct MoeArgs {
   const bf16_t* w_down;     // [E][d][Fe]
   int32_t* topk_id; float* topk_w; int32_t* pos_of;            // [n_rows*k]
   int32_t* row_of;          // [n_rows*k]: input row of each expert-sorted position
-  int32_t* counts; int32_t* offsets; int32_t* cursors;         // [E]
+  int32_t* counts; int32_t* offsets;                           // [E]
+  int32_t* blk;             // [kMoeBlocks * E] scratch of large batches
   int32_t* mtiles;          // [n_rows*k / kGroupedTileRowsMin + E] non-empty expert row tiles
   int32_t* n_mtiles;        // [1]
   int32_t* mtiles_dn;       // the same for the down projection's row tiles

@@ -82,3 +82,43 @@ def test_prefill_logits(hq, hkv, hd, length):
     err = float((got - ref).abs().max() / ref.abs().max())
     print(f"  max error over max|z|: {err:.2e}", flush=True)
     assert err <= 2e-2          # the project's bound for bf16 logits
+
+
+@pytest.mark.parametrize("experts,prompts", [(8, 130), (40, 28)])
+def test_moe_large_batch_lists_match_small_batches(experts, prompts):
+    """The routed pairs of a prefill above 16384 pairs are counted and placed by
+    several blocks, those of its halves by one.  With top-k equal to the number
+    of experts no routing can differ, so the same prompts give the same logits
+    within the bound for bf16 logits (GEMM plans depend on the batch)."""
+    print(f"moe lists E={experts} prompts={prompts}", flush=True)
+    from paper_2605_30859_amd import binding as B
+    B.load_library()
+    assert prompts // 2 * 16 * experts <= 16384 < prompts * 16 * experts
+    g = torch.Generator(device=DEV).manual_seed(experts)
+    d, q, kv, fe = 256, 256, 128, 256
+
+    def mk(fan, *shape):
+        return torch.empty(*shape, device=DEV).uniform_(-1, 1, generator=g).mul_(math.sqrt(3.0 / fan)).bfloat16()
+
+    w = [mk(1, 512, d), mk(d, 512, d), mk(d, q, d), mk(d, kv, d), mk(d, kv, d), mk(q, d, q), mk(d, experts, d),
+         mk(d, experts, fe, d), mk(d, experts, fe, d), mk(fe, experts, d, fe)]
+    mc = SimpleNamespace(n_layers=1, d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=0, vocab=512,
+                         n_experts=experts, top_k=experts, expert_ffn=fe, rope_theta=1e4, rms_eps=1e-6, dtype="bf16",
+                         weight_seed=0)
+    tokens = torch.randint(0, 512, (prompts, 16), device=DEV, generator=g, dtype=torch.int32)
+
+    def logits(part):
+        rc = SimpleNamespace(n_prompts=part.shape[0], prompt_len=16, m=2, k=2, cap=8, L=1, m_up=None, kv_pool_gb=0.0,
+                             sample_seed=1, temperature=1.0)
+        ro = B.Rollout(mc, rc, weights=w)
+        ro.darts_prefill(part.contiguous().view(-1),
+                         torch.full((2 * part.shape[0],), 100, dtype=torch.int32, device=DEV))
+        out = ro.debug_logits(part.shape[0]).double()
+        ro.close()
+        return out
+
+    whole = logits(tokens)
+    halves = torch.cat([logits(tokens[:prompts // 2]), logits(tokens[prompts // 2:])])
+    err = float((whole - halves).abs().max() / halves.abs().max())
+    print(f"  max difference over max|z|: {err:.2e}", flush=True)
+    assert err <= 2e-2

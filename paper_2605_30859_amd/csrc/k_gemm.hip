@@ -631,7 +631,7 @@ __device__ __forceinline__ int xcd_block() {
   return b;
 }
 
-template <int BM, int BN, int KB, int WGM, int WGN, int STAGES, int EPI, bool SPLIT>
+template <int BM, int BN, int KB, int WGM, int WGN, int STAGES, int EPI, bool SPLIT, int WAUX>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(const bf16_t* __restrict__ A, int lda,
                                                        const bf16_t* __restrict__ W, int ldw,
                                                        void* __restrict__ C, int ldc, int M,
@@ -639,8 +639,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_dma_kernel(const bf16_t* 
                                                        float* __restrict__ ws) {
   const int b = xcd_block();
   const int mi = b % mt, ni = (b / mt) % nt, z = b / (mt * nt);
-  dma_gemm_tile<BM, BN, KB, WGM, WGN, STAGES, EPI, SPLIT>(A, lda, W, ldw, C, ldc, M, N, k_chunk, mi,
-                                                          ni, z, ws);
+  dma_gemm_tile<BM, BN, KB, WGM, WGN, STAGES, EPI, SPLIT, false, WAUX>(A, lda, W, ldw, C, ldc, M, N, k_chunk, mi,
+                                                                       ni, z, ws);
 }
 
 // Tile order of one XCD's run of consecutive tiles: panels of kPanel row tiles,
@@ -1286,28 +1286,38 @@ static void skinny_go(const Plan& p, const void* A, int lda, const void* W, int 
                        lda, (const bf16_t*)W, ldw, C, ldc, M, N, K, K / p.S, p.nt, (float*)ws);
 }
 
+template <int EPI, int BM_, int BN_, int KB, int WGM, int WGN, int ST, bool SPLIT, int WAUX>
+static void dma_go_as(const Plan& p, const void* A, int lda, const void* W, int ldw, void* C, int ldc,
+                      int M, int N, int K, void* ws, hipStream_t st) {
+  const dim3 grid(p.mt * p.nt * p.S), blk(64 * WGM * WGN);
+  const size_t lds = (size_t)ST * (BM_ + BN_) * KB * sizeof(bf16_t);
+  static bool attr_done = false;
+  auto kern = gemm_dma_kernel<BM_, BN_, KB, WGM, WGN, ST, EPI, SPLIT, WAUX>;
+  if (!attr_done) {
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    attr_done = true;
+  }
+  hipLaunchKernelGGL(kern, grid, blk, lds, st, (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C, ldc, M, N, K,
+                     K / p.S, p.mt, p.nt, (float*)ws);
+}
+// Weights of one row tile are read by one block each: from kNtWeightBytes on,
+// too large to be found in a cache again, their loads are non-temporal.
+// Measured with weights cold, default policy against non-temporal: 8B gate/up
+// (201 MB) at 9 / 45 / 100 rows 44.1 / 39.7 / 47.5 against 38.1 / 33.9 / 42.2 us,
+// down (101 MB) 23.8 / 25.7 / 30.5 against 20.9 / 23.0 / 29.4; QKV (50 MB) gains 1
+// us up to 64 rows and loses 1 to 2 above, O (34 MB) stays, so they keep the
+// default.
+constexpr double kNtWeightBytes = 64e6;
 template <int EPI, int BM_, int BN_, int KB, int WGM, int WGN, int ST>
 static void dma_go(const Plan& p, const void* A, int lda, const void* W, int ldw, void* C, int ldc,
                    int M, int N, int K, void* ws, hipStream_t st) {
-  const dim3 grid(p.mt * p.nt * p.S), blk(64 * WGM * WGN);
-  const size_t lds = (size_t)ST * (BM_ + BN_) * KB * sizeof(bf16_t);
-  static bool attr_done[2] = {false, false};
+  const bool nt = p.mt == 1 && 2.0 * N * K >= kNtWeightBytes;
   if (p.S == 1) {
-    auto kern = gemm_dma_kernel<BM_, BN_, KB, WGM, WGN, ST, EPI, false>;
-    if (!attr_done[0]) {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      attr_done[0] = true;
-    }
-    hipLaunchKernelGGL(kern, grid, blk, lds, st, (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C,
-                       ldc, M, N, K, K, p.mt, p.nt, (float*)nullptr);
+    if (nt) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, false, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+    else dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, false, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   } else {
-    auto kern = gemm_dma_kernel<BM_, BN_, KB, WGM, WGN, ST, EPI, true>;
-    if (!attr_done[1]) {
-      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      attr_done[1] = true;
-    }
-    hipLaunchKernelGGL(kern, grid, blk, lds, st, (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C,
-                       ldc, M, N, K, K / p.S, p.mt, p.nt, (float*)ws);
+    if (nt) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+    else dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   }
 }
 

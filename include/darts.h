@@ -571,9 +571,10 @@ int darts_debug_gumbel(const float* d_u, float* d_g, int64_t n, void* stream);
  * exact map (darts_debug_gumbel) that the sampler's filter assumes; the
  * token is the exact-noise argmax provided the fast map stays within it on
  * every u = (2k+1) 2^-24, which callers can check exhaustively with these
- * two entries.  The filter's soundness argument: a thread's best fast score
- * more than twice that distance (plus float32 rounding of the sums) above
- * its second best is its exact winner; nearer cases are rescanned exactly.
+ * two entries.  The filter's soundness argument: the best fast score of a
+ * row's first logits, lowered by more than that distance (plus float32
+ * rounding of the sums), is at most the exact score of the row's winner, so
+ * no logit that a threshold there drops can win.
  * Same stream and error semantics as darts_debug_gumbel.                   */
 int darts_debug_gumbel_fast(const float* d_u, float* d_g, int64_t n, void* stream);
 float darts_sampler_gumbel_bound(void);

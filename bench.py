@@ -947,7 +947,7 @@ def main():
             moe_roof[name] = {"bound": "hbm", "achieved": ach_m, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": ach_m / HBM_PEAK_GBS, "traffic": measured_traffic(args.config, name),
                               "kernel": ("gemm_wd_grouped_kernel (gate/up + SwiGLU; gemm_dma_grouped_kernel "
-                                         "below 2 and above 96 rows per expert)") if i == 0 else
+                                         "below 2, gemm_alt_grouped_kernel above 96 rows per expert)") if i == 0 else
                                         "gemm_dma_grouped_kernel (down)",
                               "launches": n_l, "avg_launch_us": 1e3 * ms / max(n_l, 1),
                               "algorithmic_bytes_per_launch": by / max(n_l, 1),

@@ -102,6 +102,7 @@ _SIGS = {
     "darts_stream_read": (C.c_int, [_P, C.c_int64, _P, _P]),
     "darts_sampler_gumbel_bound": (C.c_float, []),
     "darts_gemm_workspace_bytes": (C.c_size_t, [C.c_int32, C.c_int32, C.c_int32]),
+    "darts_debug_gemm_plan": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_int32, _P]),
     "darts_gemm": (C.c_int, [_P, _P, _P, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                              _P, C.c_size_t, _P]),
     "darts_select_groups": (C.c_int, [_P, _P, _P, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
@@ -245,6 +246,13 @@ def darts_gemm(a, w, c, M, N, K, dtype, epilogue, workspace=None, stream=None):
     wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(load_library().darts_gemm(_ptr(a), _ptr(w), _ptr(c), M, N, K, dtype, epilogue,
                                      _ptr(workspace), wb, _stream(stream)))
+
+
+def darts_debug_gemm_plan(M, N, K, epilogue):
+    """(kind, row tiles, column tiles, K splits, alternating groups) of a bf16 darts_gemm call."""
+    out = (C.c_int32 * 5)()
+    _check(load_library().darts_debug_gemm_plan(M, N, K, epilogue, out))
+    return tuple(out)
 
 
 def darts_debug_gumbel(u, g, stream=None):

@@ -1324,6 +1324,12 @@ int darts_gemm(const void* d_a, const void* d_w, void* d_c, int32_t M, int32_t N
   return e == hipSuccess ? DARTS_OK : DARTS_EHIP;
 }
 
+int darts_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t* out) {
+  if (M < 1 || N < 1 || K < 1 || N % 128 || K % 256 || epilogue < 0 || epilogue > 3 || !out) return DARTS_EINVAL;
+  gemm_plan_info(M, N, K, epilogue, out);
+  return DARTS_OK;
+}
+
 int darts_debug_gumbel(const float* d_u, float* d_g, int64_t n, void* stream) {
   if ((!d_u || !d_g) && n > 0) return DARTS_EINVAL;
   hipError_t e = launch_gumbel_map(d_u, d_g, n, false, (hipStream_t)stream);

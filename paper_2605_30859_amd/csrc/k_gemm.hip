@@ -1139,8 +1139,8 @@ __global__ void __launch_bounds__(64 * kF32Waves) gemm_f32_kernel(const float* _
 // ------------------------------------------------------------ dispatch
 struct Plan {
   int kind;        // 0 skinny; tiled: 1 = 128x128 4 stages, 2 = 128x128 2 stages,
-                   // 3 = 256x128, 4 = 256x256, 5 = 256x192, alternating groups (3 with
-                   // short K ranges: 3 stages),
+                   // 3 = 256x128, 4 = 256x256, 5 = 256x192, alternating groups
+                   // (plan_alternates says when not),
                    // exact-fill tiles with 4 stages and 4 waves: 6 = 128x96 (4x1),
                    // 7 = 128x64 (4x1), 8 = 64x64 (2x2), 9 = 64x96 (4x1)
   int mt, nt, S;   // tiles and K splits
@@ -1319,6 +1319,41 @@ static void dma_go(const Plan& p, const void* A, int lda, const void* W, int ldw
     if (nt) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
     else dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   }
+}
+
+// The ring kernel with a large tile of the alternating groups, for matrices
+// beyond those' 32-bit offsets.
+template <int EPI, int BM_, int BN_, int WGM, int WGN>
+static void dma_far(const Plan& p, const void* A, int lda, const void* W, int ldw, void* C, int ldc, int M, int N,
+                    int K, void* ws, hipStream_t st) {
+  if (p.S == 1) dma_go_as<EPI, BM_, BN_, 64, WGM, WGN, 2, false, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+  else dma_go_as<EPI, BM_, BN_, 64, WGM, WGN, 2, true, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+}
+
+// The alternating groups address a tile's rows of A, W and C by 32-bit byte
+// offsets from its first row, so 256 rows of each have to lie within 2 GiB.
+// Longer rows (fp32 results of 2^21 columns and more, K of 2^22 and more) take
+// the ring kernel with the same tile: its addresses are 64-bit, the plan and
+// its workspace stay valid.
+static bool alt_reaches(int64_t lda, int64_t ldw, int64_t ldc, int esz) {
+  return 256 * std::max(2 * std::max(lda, ldw), esz * ldc) < ((int64_t)1 << 31);
+}
+// Whether plan p runs on the alternating groups.  256x128 tiles with short K
+// ranges of a split do not: the three-stage ring has more of the weights in
+// flight from the first K tile on (QKV of the 8B shape at 256 rows in 4 splits:
+// 27.9 against 29.3 us); whole or long ranges alternate (gate/up at 2048 rows:
+// 349 against 382 us).
+static bool plan_alternates(const Plan& p, int lda, int ldw, int ldc, int N, int K, int epi) {
+  if (p.kind < 3 || p.kind > 5) return false;
+  if (p.kind == 3 && p.S > 1 && K / p.S < 2048) return false;
+  if (p.S > 1) return alt_reaches(lda, ldw, N, 4);
+  return alt_reaches(lda, ldw, ldc, epi == EPI_BF16 || epi == EPI_SWIGLU ? 2 : 4);
+}
+
+void gemm_plan_info(int M, int N, int K, int epi, int32_t* out) {
+  const Plan p = plan_gemm(M, N, K);
+  const int32_t v[5] = {p.kind, p.mt, p.nt, p.S, plan_alternates(p, K, K, epi == EPI_SWIGLU ? N / 2 : N, N, K, epi)};
+  std::copy(v, v + 5, out);
 }
 
 template <int EPI, int BM, int BN, int WGM, int WGN>
@@ -1533,19 +1568,22 @@ static hipError_t launch_plan(const Plan& p, const void* A, int lda, const void*
       }
     }
   } else {
+    const bool alt = plan_alternates(p, lda, ldw, ldc, N, K, EPI);
     switch (p.kind) {
       case 1: dma_go<EPI, 128, 128, 64, 2, 2, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
       case 2: dma_go<EPI, 128, 128, 64, 2, 2, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
       case 3:
-        // short K ranges of a split: the three-stage ring has more of the
-        // weights in flight from the first K tile on (QKV of the 8B shape at
-        // 256 rows in 4 splits: 27.9 against 29.3 us); whole or long ranges
-        // alternate (gate/up at 2048 rows: 349 against 382 us)
-        if (p.S == 1 || K / p.S >= 2048) alt_go<EPI, 256, 128, 4, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+        if (alt) alt_go<EPI, 256, 128, 4, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
         else dma_go<EPI, 256, 128, 64, 4, 2, 3>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
         break;
-      case 4: alt_go<EPI, 256, 256, 2, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
-      case 5: alt_go<EPI, 256, 192, 4, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
+      case 4:
+        if (alt) alt_go<EPI, 256, 256, 2, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+        else dma_far<EPI, 256, 256, 2, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+        break;
+      case 5:
+        if (alt) alt_go<EPI, 256, 192, 4, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+        else dma_far<EPI, 256, 192, 4, 2>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+        break;
       case 6: dma_go<EPI, 128, 96, 64, 4, 1, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
       case 7: dma_go<EPI, 128, 64, 64, 4, 1, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;
       case 8: dma_go<EPI, 64, 64, 64, 2, 2, 4>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st); break;

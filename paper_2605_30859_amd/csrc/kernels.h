@@ -36,6 +36,9 @@ hipError_t launch_iota_perm(int32_t* stack, int64_t n, uint64_t perm_seed, bool 
 // ---- GEMM (k_gemm.hip): C[M,N] (op)= A[M,K] * W[N,K]^T
 enum Epi { EPI_F32 = 0, EPI_BF16 = 1, EPI_ADD_F32 = 2, EPI_SWIGLU = 3 };
 size_t gemm_workspace_bytes(int M, int N, int K);
+// kind, row tiles, column tiles, K splits of a bf16 GEMM's plan, and whether the
+// alternating groups run it (out: 5 values)
+void gemm_plan_info(int M, int N, int K, int epi, int32_t* out);
 // x += A . W^T and xn = bf16(RMSNorm(x)) (bf16 operands); *fused says whether
 // xn was written (split-K plans) or the caller must normalise
 // bf16 C = A . W^T in fp32 when the plan keeps K whole (*n_split = 1), else

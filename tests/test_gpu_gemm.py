@@ -168,3 +168,43 @@ def test_gemm_f32_any_size(M, N, K, epi, shift):
     err = (out[:M].double() - ref).abs()
     assert bool((err <= tol).all()), float((err - tol).max())
     assert bool((out[M:] == 3.0).all())
+
+
+@pytest.mark.parametrize("M,N,K,epi", [(259, 4500096, 256, 0), (256, 4500096, 256, 2), (259, 8601600, 256, 1),
+                                       (300, 256, 4 * 2 ** 21 + 2048, 0)])
+def test_gemm_rows_beyond_32_bit_offsets(M, N, K, epi):
+    """Rows of C or of the operands so long that 256 of them pass 4 GiB: every
+    column of the rows at both ends of the tiles, and sampled columns of every
+    row, against float64."""
+    print(f"gemm long rows M={M} N={N} K={K} epi={epi}", flush=True)
+    B = _b()
+    g = torch.Generator(device=DEV).manual_seed(N + K)
+    a = torch.empty(M, K, device=DEV, dtype=torch.bfloat16).normal_(generator=g)
+    w = torch.empty(N, K, device=DEV, dtype=torch.bfloat16).normal_(0.0, K ** -0.5, generator=g)
+    dt = torch.bfloat16 if epi == 1 else torch.float32
+    out = torch.full((M, N), 7.0, dtype=dt, device=DEV)
+    ws = torch.empty(max(B.darts_gemm_workspace_bytes(M, N, K), 256), dtype=torch.uint8, device=DEV)
+    B.darts_gemm(a, w, out, M, N, K, B.DARTS_BF16, epi, ws)
+    torch.cuda.synchronize()
+
+    def check(rows, cols):
+        ref = torch.zeros(len(rows), len(cols), dtype=torch.float64, device=DEV)
+        for k0 in range(0, K, 1 << 16):     # float64 copies of a piece of K at a time
+            ref += a[rows, k0:k0 + (1 << 16)].double() @ w[cols, k0:k0 + (1 << 16)].double().T
+        if epi == 2:
+            ref += 7.0
+        err = (out[rows][:, cols].double() - ref).abs()
+        # K roundings of partial sums of order 1, each within 2^-24: 16 times the
+        # standard deviation of their sum; 16-bit results 2^-8 more
+        tol = 16 * K ** 0.5 * 2.0 ** -24 * (ref.abs() + 1.0)
+        if epi == 1:
+            tol = tol + 2.0 ** -8 * ref.abs()
+        assert bool((err <= tol).all()), (M, N, K, epi, float((err - tol).max()))
+
+    every = torch.arange(M, device=DEV)
+    cols = torch.randint(0, N, (min(N, 512),), device=DEV, generator=g)
+    cols[0], cols[1] = 0, N - 1
+    check(every, cols)
+    ends = torch.tensor([r for r in (0, 239, 240, 255, 256, M - 1) if r < M], device=DEV)
+    for c0 in range(0, N, 1 << 20):
+        check(ends, torch.arange(c0, min(N, c0 + (1 << 20)), device=DEV))

@@ -1,0 +1,36 @@
+"""Host-side rules of the bf16 GEMM's plan (no GPU needed)."""
+import itertools
+
+import pytest
+
+from paper_2605_30859_amd import binding as B
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    B.load_library()
+
+
+def test_large_tiles_stay_within_32_bit_offsets():
+    """The persistent large-tile kernel addresses 256 rows of A, W and C by 32-bit
+    byte offsets: no plan may give it rows that reach 2 GiB, whether they are
+    the operands' (K), the result's or a split's fp32 partial sums."""
+    edges = [2 ** p + d for p in (20, 21, 22) for d in (-768, -256, 0, 256)]
+    ns = [1024, 4096, 24576] + edges + [2 ** 22 + 2 ** 19, 2 ** 23, 2 ** 24]
+    ks = [256, 2048, 4096] + edges + [2 ** 22 + 2048, 2 ** 23, 2 ** 24]
+    taken = 0
+    for m, n, k, epi in itertools.product((129, 256, 257, 512, 4096, 16384), ns, ks, range(4)):
+        kind, mt, nt, split, alt = B.darts_debug_gemm_plan(m, n, k, epi)
+        if not alt:
+            continue
+        taken += 1
+        ldc, size = (n, 4) if split > 1 or epi in (0, 2) else (n // 2, 2) if epi == 3 else (n, 2)
+        assert 256 * max(2 * k, size * ldc) < 2 ** 31, (m, n, k, epi, kind, split)
+    assert taken > 200
+
+
+@pytest.mark.parametrize("m,n,k,epi", [(389, 24576, 4096, 3), (16384, 24576, 4096, 3), (4096, 6144, 4096, 0),
+                                       (2048, 4096, 12288, 2), (512, 151936, 4096, 0), (4096, 2 ** 21 - 256, 256, 0)])
+def test_large_tiles_run_ordinary_shapes(m, n, k, epi):
+    """The projections of the supported decoders, and the widest rows in reach."""
+    assert B.darts_debug_gemm_plan(m, n, k, epi)[4] == 1

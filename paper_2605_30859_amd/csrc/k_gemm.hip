@@ -314,13 +314,17 @@ __device__ __forceinline__ void vm_lgkm_wait() {   // vmcnt(N) and lgkmcnt(0)
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4));
 }
-// A raw barrier that neither memory accesses nor MFMAs are moved across.
+// Neither memory accesses nor MFMAs are moved across.
+__device__ __forceinline__ void order_fence() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// The same with a raw barrier.
 __device__ __forceinline__ void fenced_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  asm volatile("" ::: "memory");
+  order_fence();
   __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
+  order_fence();
 }
 
 // One output tile of alt_gemm_items.
@@ -554,6 +558,7 @@ __device__ __forceinline__ void alt_gemm_items(int lda, int ldw, int ldc, int nk
       cur = nxt;
       start();
     }
+    order_fence();   // landed() counts the stores below as younger than start()'s loads
     // accumulators: row 16*i + lane%16, columns 16*j + 4*(lane/16) .. +3, or with
     // kPair those of tiles j, j + 1 columns 16*j + 8*(lane/16) .. +7
     auto store = [&](int h, int i) {

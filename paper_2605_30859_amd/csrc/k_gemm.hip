@@ -43,8 +43,6 @@ namespace darts {
 
 
 __device__ __forceinline__ float silu_f(float g) { return g / (1.0f + __expf(-g)); }
-// the same with the hardware reciprocal (within 1 ulp of the quotient)
-__device__ __forceinline__ float silu_fast(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 template <int EPI>
 __device__ __forceinline__ void epi_store(void* C, int ldc, int M, int m, int n, float v) {
@@ -298,8 +296,7 @@ __device__ __forceinline__ void dma_gemm_tile(const bf16_t* __restrict__ A, int 
 // consecutive columns of one output row and the epilogue stores them together.
 // For SwiGLU B0 holds the gate rows and B1 the up rows of the tile's columns,
 // so a lane has both of a feature.  The sums run over K in the same order as
-// in dma_gemm_tile, so results are bitwise those of the tiled kernel (but for
-// the SwiGLU epilogue's reciprocal).
+// in dma_gemm_tile, so results are bitwise those of the tiled kernel.
 //
 // Bound by the matrix cores, at the clock that the card's power allows: a
 // library GEMM of the same sizes reaches 1530 TFLOP/s.  Measured on the
@@ -572,7 +569,7 @@ __device__ __forceinline__ void alt_gemm_items(int lda, int ldw, int ldc, int nk
             f32x4_t u = acc[h][g][i][j];
             if constexpr (kSwiglu) {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) u[e] = silu_fast(u[e]) * acc[h][1][i][j][e];
+              for (int e = 0; e < 4; ++e) u[e] = silu_f(u[e]) * acc[h][1][i][j][e];
             }
             v[j] = make_uint2(f32_to_bf16x2(u[0], u[1]), f32_to_bf16x2(u[2], u[3]));
           }

@@ -208,3 +208,28 @@ def test_gemm_rows_beyond_32_bit_offsets(M, N, K, epi):
     ends = torch.tensor([r for r in (0, 239, 240, 255, 256, M - 1) if r < M], device=DEV)
     for c0 in range(0, N, 1 << 20):
         check(ends, torch.arange(c0, min(N, c0 + (1 << 20)), device=DEV))
+
+
+@pytest.mark.parametrize("M,kind", [(129, 3), (300, 5), (1100, 4)])
+@pytest.mark.parametrize("scale", [1.0, 30.0])
+def test_swiglu_rows_do_not_depend_on_the_tile(M, kind, scale):
+    """The SwiGLU projection in 256-row tiles (256x128, 256x192, 256x256) and in
+    128-row tiles: while neither plan splits K, the sums run over K in the same
+    order and a row's results are the same bit for bit.  scale 30: gates down to
+    -100, where the quotient g / (1 + e^-g) becomes small and then zero."""
+    print(f"swiglu tiles M={M} kind={kind} scale={scale}", flush=True)
+    B = _b()
+    N, K, part = 24576, 512, 100
+    assert B.darts_debug_gemm_plan(M, N, K, 3)[::2] == (kind, N // {3: 128, 4: 256, 5: 192}[kind], 1)
+    assert B.darts_debug_gemm_plan(M, N, K, 3)[3] == 1 and B.darts_debug_gemm_plan(part, N, K, 3)[3:] == (1, 0)
+    g = torch.Generator(device=DEV).manual_seed(M)
+    a = (torch.randn(M, K, device=DEV, generator=g) * scale).bfloat16()
+    w = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).bfloat16()
+    whole = torch.empty(M, N // 2, dtype=torch.bfloat16, device=DEV)
+    rows = torch.empty(part, N // 2, dtype=torch.bfloat16, device=DEV)
+    B.darts_gemm(a, w, whole, M, N, K, B.DARTS_BF16, 3)
+    for r0 in (0, M - part):
+        B.darts_gemm(a[r0:r0 + part], w, rows, part, N, K, B.DARTS_BF16, 3)
+        torch.cuda.synchronize()
+        same = whole[r0:r0 + part].view(torch.int16) == rows.view(torch.int16)
+        assert bool(same.all()), (M, kind, scale, r0, int((~same).sum()))

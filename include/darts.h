@@ -559,9 +559,10 @@ int darts_gemm(const void* d_a, const void* d_w, void* d_c, int32_t M, int32_t N
                int32_t dtype, int32_t epilogue, void* d_workspace, size_t workspace_bytes,
                void* stream);
 
-/* The launch plan of a bf16 darts_gemm call (host only): out[0..4] = kernel
- * kind, row tiles, column tiles, K splits, and 1 if the persistent large-tile
- * kernel runs it.  For tests of the planner's limits.                       */
+/* The launch plan of a bf16 darts_gemm call (host only): out[0..5] = kernel
+ * kind, row tiles, column tiles, K splits, 1 if the persistent large-tile
+ * kernel runs it, and 1 if its weights are loaded non-temporal.  For tests of
+ * the planner's limits.                                                     */
 int darts_debug_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t* out);
 
 /* Gumbel noise map used by darts_sample: d_g[i] = -ln(-ln(d_u[i])) with the

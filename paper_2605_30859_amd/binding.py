@@ -249,8 +249,9 @@ def darts_gemm(a, w, c, M, N, K, dtype, epilogue, workspace=None, stream=None):
 
 
 def darts_debug_gemm_plan(M, N, K, epilogue):
-    """(kind, row tiles, column tiles, K splits, alternating groups) of a bf16 darts_gemm call."""
-    out = (C.c_int32 * 5)()
+    """(kind, row tiles, column tiles, K splits, alternating groups, non-temporal weights) of a bf16
+    darts_gemm call."""
+    out = (C.c_int32 * 6)()
     _check(load_library().darts_debug_gemm_plan(M, N, K, epilogue, out))
     return tuple(out)
 

@@ -58,6 +58,7 @@ struct darts_ctx {
   size_t esz = 4;
   int P = 0, Lp = 0, cap = 0, pp = 0, max_pages = 0, n_traj = 0;
   int64_t n_pages = 0;
+  double pass_bytes = 0.0;   // dense weights that a step reads, once each
   int d = 0, hq = 0, hkv = 0, hd = 0, F = 0, V = 0, nl = 0, qkv_w = 0;
   bool moe = false;
   int E = 0, topk = 0, Fe = 0, Epad = 0;   // Epad: router rows padded to a multiple of 128
@@ -468,6 +469,8 @@ int darts_init(const darts_model_cfg* model, int32_t m, int32_t k, const darts_r
   c->F = moe ? 0 : mc.ffn_dim; c->V = mc.vocab; c->nl = mc.n_layers; c->qkv_w = qkv_w;
   c->moe = moe; c->E = mc.n_experts; c->topk = mc.top_k; c->Fe = mc.expert_ffn;
   c->Epad = (c->E + 127) / 128 * 128;
+  c->pass_bytes = (double)c->esz * c->d *
+                  (c->nl * ((double)qkv_w + c->hq * c->hd + 3.0 * c->F) + (double)c->V);
 
   const int64_t page_bytes_all = (int64_t)c->nl * c->hkv * kPage * c->hd * 2 * c->esz;
   const int64_t worst = (int64_t)c->P * c->pp + (int64_t)c->n_traj * ((c->cap + kPage - 1) / kPage);
@@ -752,7 +755,7 @@ static hipError_t gemm_t(darts_ctx* c, int cls, const void* A, int lda, const vo
                          void* C, int ldc, int M, int N, int K, int epi) {
   const int ti = tbegin(c, 1 + cls, 2.0 * M * N * K);
   hipError_t e = launch_gemm(c->bf16, A, lda, W, ldw, C, ldc, M, N, K, epi, c->gemm_ws,
-                             c->gemm_ws_bytes, c->st);
+                             c->gemm_ws_bytes, c->st, c->pass_bytes);
   tend(c, ti);
   return e;
 }
@@ -765,7 +768,7 @@ static hipError_t gemm_add_t(darts_ctx* c, int cls, const void* A, int lda, cons
   hipError_t e;
   if (c->bf16) {
     e = launch_gemm_add_norm(A, lda, W, ldw, c->x, c->d, M, c->d, K, c->gemm_ws, c->gemm_ws_bytes,
-                             c->mc.rms_eps, c->xn, c->st, normed);
+                             c->mc.rms_eps, c->xn, c->st, normed, c->pass_bytes);
   } else {
     *normed = false;
     e = launch_gemm(false, A, lda, W, ldw, c->x, c->d, M, c->d, K, EPI_ADD_F32, c->gemm_ws,
@@ -794,7 +797,7 @@ static int run_layers(darts_ctx* c, int n, const int32_t* row_pt, const int32_t*
     if (b) {
       const int ti = tbegin(c, 1 + G_QKV, 2.0 * n * c->qkv_w * d);
       HIPCHK(c, launch_gemm_f32_or_partials(c->xn, d, w.wqkv, d, c->qkv, c->qkv_w, n, c->qkv_w, d,
-                                            c->gemm_ws, c->gemm_ws_bytes, c->st, &n_split));
+                                            c->gemm_ws, c->gemm_ws_bytes, c->st, &n_split, c->pass_bytes));
       tend(c, ti);
       if (n_split > 1) qkv_src = (const float*)c->gemm_ws;
     } else {
@@ -882,7 +885,7 @@ int darts_prefill(darts_ctx* c, const int32_t* d_prompts, const int32_t* d_force
   HIPCHK(c, launch_gather_rows(c->x, c->last_rows, c->P, c->d, c->xlast, c->st));
   HIPCHK(c, launch_rmsnorm(c->xlast, c->P, c->d, c->mc.rms_eps, c->xn, b, c->st));
   HIPCHK(c, launch_gemm(b, c->xn, c->d, c->lm_head, c->d, c->logits, c->V, c->P, c->V, c->d,
-                        EPI_F32, c->gemm_ws, c->gemm_ws_bytes, c->st));
+                        EPI_F32, c->gemm_ws, c->gemm_ws_bytes, c->st, c->pass_bytes));
   SampleArgs a{};
   a.logits = c->logits; a.n_rows = c->n_start; a.vocab = c->V; a.bf16 = false;
   a.seed = c->rc.sample_seed; a.temperature = c->rc.temperature; a.traj_base = c->rc.traj_base;

@@ -1147,6 +1147,7 @@ struct Plan {
                    // 7 = 128x64 (4x1), 8 = 64x64 (2x2), 9 = 64x96 (4x1)
   int mt, nt, S;   // tiles and K splits
   int MT, NS;      // skinny shape
+  bool nt_w;       // weights loaded non-temporal (tiled kernels; set per call, see stream_weights)
 };
 
 // Planning assumes MI355X's 256 CUs whatever device runs the call, so a
@@ -1260,6 +1261,25 @@ static Plan plan_gemm(int M, int N, int K) {
   return p;
 }
 
+// Non-temporal weight loads: for weights that one row tile reads once and that
+// no cache holds when they come round again.  pass_bytes are what the caller
+// reads between two uses of W (0: unknown, W itself may come next), and the
+// Infinity Cache is 256 MiB.  Measured, default policy against non-temporal:
+// read again at once, 8B gate/up (201 MB) at 45 rows 31.4 against 39.4 us, down
+// (101 MB) 20.0 against 22.4, 268 MB 43.3 against 57; from 302 MB on, non-temporal
+// is ahead either way (302 MB 76.3 / 75.2, 403 MB 91.4 / 78.8).  Behind other
+// weights (a decoder's pass) it gains 2-10% from 64 MB on up to 48 rows (down at
+// 45 rows 24.7 / 23.4), and up to 128 rows between 128 and 450 MB (gate/up at 128
+// rows 2%, 134 MB 5%, 403 MB 8%); below and above that more rows lose (67 MB at 100
+// rows 20.9 / 23.8, LM head of the 8B shape at 100 rows 258 / 268).
+constexpr double kNtWeightBytes = 64e6, kNtPassBytes = 300e6, kNtMidFrom = 128e6, kNtMidTo = 450e6;
+constexpr int kNtRows = 48, kNtMidRows = 128;
+static bool stream_weights(int M, int N, int K, double pass_bytes) {
+  const double w = 2.0 * N * K;
+  return M <= (w >= kNtMidFrom && w <= kNtMidTo ? kNtMidRows : kNtRows) && w >= kNtWeightBytes &&
+         std::max(w, pass_bytes) >= kNtPassBytes;
+}
+
 size_t gemm_workspace_bytes(int M, int N, int K) {
   const Plan p = plan_gemm(M, N, K);
   return p.S > 1 ? (size_t)p.S * M * N * sizeof(float) : 0;
@@ -1302,23 +1322,14 @@ static void dma_go_as(const Plan& p, const void* A, int lda, const void* W, int 
   hipLaunchKernelGGL(kern, grid, blk, lds, st, (const bf16_t*)A, lda, (const bf16_t*)W, ldw, C, ldc, M, N, K,
                      K / p.S, p.mt, p.nt, (float*)ws);
 }
-// Weights of one row tile are read by one block each: from kNtWeightBytes on,
-// too large to be found in a cache again, their loads are non-temporal.
-// Measured with weights cold, default policy against non-temporal: 8B gate/up
-// (201 MB) at 9 / 45 / 100 rows 44.1 / 39.7 / 47.5 against 38.1 / 33.9 / 42.2 us,
-// down (101 MB) 23.8 / 25.7 / 30.5 against 20.9 / 23.0 / 29.4; QKV (50 MB) gains 1
-// us up to 64 rows and loses 1 to 2 above, O (34 MB) stays, so they keep the
-// default.
-constexpr double kNtWeightBytes = 64e6;
 template <int EPI, int BM_, int BN_, int KB, int WGM, int WGN, int ST>
 static void dma_go(const Plan& p, const void* A, int lda, const void* W, int ldw, void* C, int ldc,
                    int M, int N, int K, void* ws, hipStream_t st) {
-  const bool nt = p.mt == 1 && 2.0 * N * K >= kNtWeightBytes;
   if (p.S == 1) {
-    if (nt) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, false, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+    if (p.nt_w) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, false, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
     else dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, false, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   } else {
-    if (nt) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
+    if (p.nt_w) dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, kNtLoad>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
     else dma_go_as<EPI, BM_, BN_, KB, WGM, WGN, ST, true, 0>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   }
 }
@@ -1354,8 +1365,9 @@ static bool plan_alternates(const Plan& p, int lda, int ldw, int ldc, int N, int
 
 void gemm_plan_info(int M, int N, int K, int epi, int32_t* out) {
   const Plan p = plan_gemm(M, N, K);
-  const int32_t v[5] = {p.kind, p.mt, p.nt, p.S, plan_alternates(p, K, K, epi == EPI_SWIGLU ? N / 2 : N, N, K, epi)};
-  std::copy(v, v + 5, out);
+  const int32_t v[6] = {p.kind, p.mt, p.nt, p.S, plan_alternates(p, K, K, epi == EPI_SWIGLU ? N / 2 : N, N, K, epi),
+                        p.kind > 0 && stream_weights(M, N, K, 0.0)};
+  std::copy(v, v + 6, out);
 }
 
 template <int EPI, int BM, int BN, int WGM, int WGN>
@@ -1597,8 +1609,10 @@ static hipError_t launch_plan(const Plan& p, const void* A, int lda, const void*
 
 template <int EPI>
 static hipError_t gemm_bf16_launch(const void* A, int lda, const void* W, int ldw, void* C, int ldc,
-                                   int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st) {
-  const Plan p = plan_gemm(M, N, K);
+                                   int M, int N, int K, void* ws, size_t ws_bytes, hipStream_t st,
+                                   double pass_bytes) {
+  Plan p = plan_gemm(M, N, K);
+  p.nt_w = stream_weights(M, N, K, pass_bytes);
   if (p.S > 1 && (ws == nullptr || ws_bytes < (size_t)p.S * M * N * sizeof(float)))
     return hipErrorInvalidValue;
   hipError_t e = launch_plan<EPI>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
@@ -1628,7 +1642,8 @@ static hipError_t gemm_f32_launch(const void* A, int lda, const void* W, int ldw
 }
 
 hipError_t launch_gemm(bool bf16, const void* A, int lda, const void* W, int ldw, void* C, int ldc,
-                       int M, int N, int K, int epi, void* ws, size_t ws_bytes, hipStream_t st) {
+                       int M, int N, int K, int epi, void* ws, size_t ws_bytes, hipStream_t st,
+                       double pass_bytes) {
   if (M <= 0) return hipSuccess;
   if (!bf16) {
     switch (epi) {
@@ -1641,23 +1656,24 @@ hipError_t launch_gemm(bool bf16, const void* A, int lda, const void* W, int ldw
   }
   if (N % 128 != 0 || K % 256 != 0) return hipErrorInvalidValue;
   switch (epi) {
-    case EPI_F32: return gemm_bf16_launch<EPI_F32>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st);
-    case EPI_BF16: return gemm_bf16_launch<EPI_BF16>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st);
+    case EPI_F32: return gemm_bf16_launch<EPI_F32>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st, pass_bytes);
+    case EPI_BF16: return gemm_bf16_launch<EPI_BF16>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st, pass_bytes);
     case EPI_ADD_F32:
-      return gemm_bf16_launch<EPI_ADD_F32>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st);
+      return gemm_bf16_launch<EPI_ADD_F32>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st, pass_bytes);
     case EPI_SWIGLU:
-      return gemm_bf16_launch<EPI_SWIGLU>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st);
+      return gemm_bf16_launch<EPI_SWIGLU>(A, lda, W, ldw, C, ldc, M, N, K, ws, ws_bytes, st, pass_bytes);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_f32_or_partials(const void* A, int lda, const void* W, int ldw, float* C,
                                        int ldc, int M, int N, int K, void* ws, size_t ws_bytes,
-                                       hipStream_t st, int* n_split) {
+                                       hipStream_t st, int* n_split, double pass_bytes) {
   *n_split = 1;
   if (M <= 0) return hipSuccess;
   if (N % 128 != 0 || K % 256 != 0) return hipErrorInvalidValue;
-  const Plan p = plan_gemm(M, N, K);
+  Plan p = plan_gemm(M, N, K);
+  p.nt_w = stream_weights(M, N, K, pass_bytes);
   if (p.S == 1) return launch_plan<EPI_F32>(p, A, lda, W, ldw, C, ldc, M, N, K, ws, st);
   if (ws == nullptr || ws_bytes < (size_t)p.S * M * N * sizeof(float)) return hipErrorInvalidValue;
   *n_split = p.S;
@@ -1669,13 +1685,14 @@ hipError_t launch_gemm_f32_or_partials(const void* A, int lda, const void* W, in
 // otherwise the GEMM adds in its epilogue and the caller normalises.
 hipError_t launch_gemm_add_norm(const void* A, int lda, const void* W, int ldw, float* x, int ldx,
                                 int M, int N, int K, void* ws, size_t ws_bytes, float eps,
-                                void* xn, hipStream_t st, bool* fused) {
+                                void* xn, hipStream_t st, bool* fused, double pass_bytes) {
   *fused = false;
   if (M <= 0) return hipSuccess;
   if (N % 128 != 0 || K % 256 != 0) return hipErrorInvalidValue;
-  const Plan p = plan_gemm(M, N, K);
+  Plan p = plan_gemm(M, N, K);
+  p.nt_w = stream_weights(M, N, K, pass_bytes);
   if (p.S == 1 || p.S > kMaxSplits || N > kAddNormMaxN)
-    return gemm_bf16_launch<EPI_ADD_F32>(A, lda, W, ldw, x, ldx, M, N, K, ws, ws_bytes, st);
+    return gemm_bf16_launch<EPI_ADD_F32>(A, lda, W, ldw, x, ldx, M, N, K, ws, ws_bytes, st, pass_bytes);
   if (ws == nullptr || ws_bytes < (size_t)p.S * M * N * sizeof(float)) return hipErrorInvalidValue;
   // the partial-sum GEMM of the plan, then the fused reduce
   hipError_t e = launch_plan<EPI_ADD_F32>(p, A, lda, W, ldw, x, ldx, M, N, K, ws, st);

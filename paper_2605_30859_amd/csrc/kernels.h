@@ -36,21 +36,25 @@ hipError_t launch_iota_perm(int32_t* stack, int64_t n, uint64_t perm_seed, bool 
 // ---- GEMM (k_gemm.hip): C[M,N] (op)= A[M,K] * W[N,K]^T
 enum Epi { EPI_F32 = 0, EPI_BF16 = 1, EPI_ADD_F32 = 2, EPI_SWIGLU = 3 };
 size_t gemm_workspace_bytes(int M, int N, int K);
-// kind, row tiles, column tiles, K splits of a bf16 GEMM's plan, and whether the
-// alternating groups run it (out: 5 values)
+// kind, row tiles, column tiles, K splits of a bf16 GEMM's plan, whether the
+// alternating groups run it, and whether a stateless call's weight loads are
+// non-temporal (out: 6 values)
 void gemm_plan_info(int M, int N, int K, int epi, int32_t* out);
+// pass_bytes: at least so many bytes are read between two uses of these weights
+// (a decoder's weights from one step to the next); 0: not known.
 // x += A . W^T and xn = bf16(RMSNorm(x)) (bf16 operands); *fused says whether
 // xn was written (split-K plans) or the caller must normalise
 // bf16 C = A . W^T in fp32 when the plan keeps K whole (*n_split = 1), else
 // only the plan's split-K partial sums into ws (*n_split planes of M*N floats)
 hipError_t launch_gemm_f32_or_partials(const void* A, int lda, const void* W, int ldw, float* C,
                                        int ldc, int M, int N, int K, void* ws, size_t ws_bytes,
-                                       hipStream_t st, int* n_split);
+                                       hipStream_t st, int* n_split, double pass_bytes = 0.0);
 hipError_t launch_gemm_add_norm(const void* A, int lda, const void* W, int ldw, float* x, int ldx,
                                 int M, int N, int K, void* ws, size_t ws_bytes, float eps,
-                                void* xn, hipStream_t st, bool* fused);
+                                void* xn, hipStream_t st, bool* fused, double pass_bytes = 0.0);
 hipError_t launch_gemm(bool bf16, const void* A, int lda, const void* W, int ldw, void* C, int ldc,
-                       int M, int N, int K, int epi, void* ws, size_t ws_bytes, hipStream_t st);
+                       int M, int N, int K, int epi, void* ws, size_t ws_bytes, hipStream_t st,
+                       double pass_bytes = 0.0);
 
 // ---- elementwise (k_elem.hip)
 // embedding gather; with xn != NULL (bf16 models) also xn = bf16(RMSNorm(x))

@@ -20,7 +20,7 @@ def test_large_tiles_stay_within_32_bit_offsets():
     ks = [256, 2048, 4096] + edges + [2 ** 22 + 2048, 2 ** 23, 2 ** 24]
     taken = 0
     for m, n, k, epi in itertools.product((129, 256, 257, 512, 4096, 16384), ns, ks, range(4)):
-        kind, mt, nt, split, alt = B.darts_debug_gemm_plan(m, n, k, epi)
+        kind, _, _, split, alt, _ = B.darts_debug_gemm_plan(m, n, k, epi)
         if not alt:
             continue
         taken += 1
@@ -34,3 +34,13 @@ def test_large_tiles_stay_within_32_bit_offsets():
 def test_large_tiles_run_ordinary_shapes(m, n, k, epi):
     """The projections of the supported decoders, and the widest rows in reach."""
     assert B.darts_debug_gemm_plan(m, n, k, epi)[4] == 1
+
+
+@pytest.mark.parametrize("m,n,k,nt", [(45, 24576, 4096, 0), (45, 4096, 12288, 0), (9, 32768, 4096, 0), (9, 36864, 4096, 1),
+                                      (16, 151936, 4096, 1), (48, 151936, 2048, 1), (49, 151936, 2048, 0),
+                                      (128, 24576, 8192, 1), (129, 24576, 8192, 0)])
+def test_weights_that_a_cache_may_hold_are_loaded_normally(m, n, k, nt):
+    """A stateless call may be repeated with the same weights: only those that the
+    256 MiB Infinity Cache cannot keep are loaded non-temporal, and only for
+    batches where that was measured to gain."""
+    assert B.darts_debug_gemm_plan(m, n, k, 0)[5] == nt

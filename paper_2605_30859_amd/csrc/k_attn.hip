@@ -23,6 +23,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "kernels.h"
@@ -869,20 +870,42 @@ static int attn_slots(int hd) {
   return cached[i];
 }
 
+// Estimated time (us, less what every split has) of an equal-context launch in n
+// chunks of c pages per row.  A wavefront spends kTau per page when few run; the
+// pages of w wavefronts take w * c * page bytes / kBw when many do (a tenth of
+// them counted by whole blocks per CU); in between the two add up in cubes.  A last round after full ones costs at least
+// kLastRound of a full one.  Split rows pay for the combine launch, its
+// wavefronts (one per row and query head) and the partial sums.
+static double chunk_estimate(int n_rows, int hq, int hkv, int hd, int slots, int64_t n, int c) {
+  constexpr double kBw = 6.7e6, kStart = 0.9, kLastRound = 0.4;           // bytes/us, us
+  constexpr double kCombine = 3.1, kCombineRow = 4e-4, kPartBw = 3.5e6;   // us, us, bytes/us
+  const double tau = 0.33 + 0.0038 * hd, page = 4.0 * kPage * hd;         // us, bytes
+  const double lat = (c + (c & 1)) * tau + kStart;
+  auto round = [&](double w) {
+    const double full_cus = std::ceil(w / (4 * 256)) * (4 * 256);
+    const double bw = (w > 4 * 256 ? w + 0.1 * (full_cus - w) : w) * c * page / kBw;
+    return std::cbrt(lat * lat * lat + bw * bw * bw);
+  };
+  const int64_t items = (int64_t)n_rows * hkv * n, full = items / slots, rest = items - full * slots;
+  double t = full > 0 ? (double)full * round(slots) : 0.0;
+  if (rest > 0) t += full > 0 ? std::max(round((double)rest), kLastRound * round(slots)) : round((double)rest);
+  if (n > 1) t += kCombine + kCombineRow * n_rows * hq + 8.0 * (double)n * n_rows * hq * hd / kPartBw;
+  return t;
+}
+
 // Pages per chunk.  Ragged contexts: 128 pages (2048 keys), so that the
 // longest rows are spread over many wavefronts instead of one while short rows
 // stay whole (on the sweep's lognormal contexts, 32 / 64 / 128 / 256 pages
 // took 1.85 / 1.76 / 1.72 / 1.82 ms: fewer chunks mean fewer partial sums and
-// less per-item work, more mean better balance).  Equal contexts: the
-// chunk count that minimises the kernel's makespan, rounds of resident
-// wavefronts times pages per chunk (plus a page of fixed work per item), where a
-// last round after full ones counts for as much as it fills, at least half (777
-// rows x 4 kv heads in whole rows: 300 us; in 3 chunks, which whole rounds
-// favour: 346), plus
-// the partial-sum round trip and combine launch when rows are split; at most
-// ~4 rounds of items and chunks of at least 4 pages.
+// less per-item work, more mean better balance).  Equal contexts: the chunk
+// count with the least estimated time, at most ~4 rounds of items and chunks of
+// at least 4 pages.  The estimate's figures were fitted to 2200 forced splits of
+// 580 sizes (1 to 1024 rows, 40 to 12000 keys; 32/8, 32/4 heads x 128, 16/4 x
+// 64, 32/8 x 32).  Its choices take 0.5-0.9% more than the fastest split on
+// average; counting whole or partial rounds alone took 5% more, and up to 1.5
+// times as long (450 rows x 120 keys, 16/4 x 64: whole rows 13.1 us, halves 22.2).
 constexpr int kRaggedChunkPages = 128;
-static int choose_chunk_pages(int n_rows, int hkv, int max_ctx, bool uniform, int hd) {
+static int choose_chunk_pages(int n_rows, int hq, int hkv, int max_ctx, bool uniform, int hd) {
   const int64_t units = (int64_t)n_rows * hkv;
   const int npg = (max_ctx + kPage - 1) / kPage;
   if (!uniform) return npg <= kRaggedChunkPages ? npg + (npg & 1) : kRaggedChunkPages;
@@ -895,12 +918,7 @@ static int choose_chunk_pages(int n_rows, int hkv, int max_ctx, bool uniform, in
     const int64_t nch = (npg + c - 1) / c;
     if (nch != n) continue;                 // same split as a smaller n
     if (n > 1 && c < 4) break;              // chunks of at least 4 pages (64 keys)
-    const double items = (double)units * nch;
-    // a last round that is not full has the memory to itself: its wavefronts
-    // run up to about twice as fast
-    const double full = std::floor(items / slots), rest = items / slots - full;
-    double t = (full + (rest <= 0.0 ? 0.0 : full < 1.0 ? 1.0 : std::max(rest, 0.5))) * (c + 1.0);
-    if (nch > 1) t += 0.5 * items / slots + 3.0;
+    const double t = chunk_estimate(n_rows, hq, hkv, hd, slots, n, c);
     if (t < best) { best = t; best_c = c; }
   }
   return best_c;
@@ -980,7 +998,7 @@ hipError_t launch_attention_spec(const void* q, const void* k_pool, const void* 
   const size_t need = ws_layout(n_rows, hq, hkv, hd, max_ctx, 0, (char*)ws, &w);
   if (ws == nullptr || ws_bytes < need) return hipErrorInvalidValue;
   const bool uniform = bf16 && cs.ctx_len == nullptr && cs.mod == 0;
-  const int cp = choose_chunk_pages(n_rows, hkv, max_ctx, uniform, hd);
+  const int cp = choose_chunk_pages(n_rows, hq, hkv, max_ctx, uniform, hd);
   const int uni_nch = uniform ? ((min(cs.base, max_ctx) + cp * kPage - 1) / (cp * kPage)) : 0;
   if (!uniform)
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, cs, n_rows, cp * kPage,
@@ -1073,7 +1091,7 @@ hipError_t launch_attention_shared(const void* q, const void* k_pool, const void
   int64_t gpre = std::min<int64_t>(std::max<int64_t>((pre_items + 3) / 4, 1), 2048);
   // per-row kernel over the keys after the prefix
   const int span = ctx - cs.skip;
-  const int cp = choose_chunk_pages(n_rows, hkv, span, true, hd);
+  const int cp = choose_chunk_pages(n_rows, hq, hkv, span, true, hd);
   const int nch = (span + cp * kPage - 1) / (cp * kPage);
   if ((int64_t)n_rows * nch > w.max_chunks) return hipErrorInvalidValue;
   AttnBf16Args a;

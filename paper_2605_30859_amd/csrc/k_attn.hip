@@ -40,8 +40,11 @@ struct CtxSpec {
                            // multiple of 16; 0 when prefixes are not shared)
   int pt_rows;             // row_pt values are clamped into [0, pt_rows) when > 0
   int nt_from;             // pages from this index of a row's list on are the row's alone: their
-                           // loads are non-temporal
+                           // loads are non-temporal; -1: the kernel looks
 };
+// KV bytes of a call from which unshared pages are loaded non-temporal when the
+// caller may come back with the same pools: the size of the Infinity Cache
+constexpr double kNtKvBytes = 256e6;
 __device__ __forceinline__ int pt_row(const CtxSpec& c, int r) {
   if (!c.row_pt) return r;
   const int v = c.row_pt[r];
@@ -57,35 +60,37 @@ __device__ __forceinline__ int clamp_page(const CtxSpec& c, int p) {
   return (int)min((int64_t)max(p, 0), c.n_pages - 1);
 }
 
-// Single block: per-row chunk counts -> exclusive offsets and the work list.
+// Single block: per-row chunk counts -> exclusive offsets and the work list
+// (*info items), and info[1] = whether the rows' keys come to nt_keys or more.
 __global__ void attn_plan_kernel(CtxSpec cs, int n_rows, int chunk_tokens, int32_t* chunk_off,
-                                 int2* work, int32_t* info) {
-  __shared__ int32_t sums[1024];
-  __shared__ int32_t running;
+                                 int2* work, int32_t* info, int64_t nt_keys) {
+  __shared__ int32_t sh[32];
+  __shared__ unsigned long long keys;
   const int tid = threadIdx.x;
-  if (tid == 0) running = 0;
-  __syncthreads();
+  if (tid == 0) keys = 0;      // (the scans' barriers publish it)
+  unsigned long long mine = 0;
+  int running = 0;
   for (int base = 0; base < n_rows; base += 1024) {
     const int r = base + tid;
-    const int c = r < n_rows ? (span_of(cs, r) + chunk_tokens - 1) / chunk_tokens : 0;
-    sums[tid] = c;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {     // inclusive Hillis-Steele scan
-      const int v = tid >= o ? sums[tid - o] : 0;
-      __syncthreads();
-      sums[tid] += v;
-      __syncthreads();
-    }
-    const int excl = running + sums[tid] - c;
+    const int span = r < n_rows ? span_of(cs, r) : 0;
+    const int c = (span + chunk_tokens - 1) / chunk_tokens;
+    mine += span;
+    int total;
+    const int excl = running + block_excl_scan1024(c, sh, &total);
     if (r < n_rows) {
       chunk_off[r] = excl;
       for (int j = 0; j < c; ++j) work[excl + j] = make_int2(r, j);
     }
-    __syncthreads();
-    if (tid == 1023) running += sums[1023];
-    __syncthreads();
+    running += total;
   }
-  if (tid == 0) info[0] = running;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+  if ((tid & 63) == 0 && mine > 0) atomicAdd(&keys, mine);
+  __syncthreads();
+  if (tid == 0) {
+    info[0] = running;
+    info[1] = (int64_t)keys >= nt_keys ? 1 : 0;
+  }
 }
 
 // Single block: row ranges of the prompt groups in a row list sorted by
@@ -312,6 +317,8 @@ __global__ void __launch_bounds__(256) attn_bf16_kernel(AttnBf16Args A) {
   const int quad = lane >> 4, col = lane & 15;
   const int total = (A.uniform_nch > 0 ? A.n_rows * A.uniform_nch : A.info[0]) * hkv;
   const int skip_pages = A.cs.skip / kPage;
+  // ragged rows: the host knows their largest context only, the plan their sum
+  const int nt_all = A.uniform_nch > 0 || A.cs.nt_from >= 0 || A.info[1] ? A.cs.nt_from : INT32_MAX;
   bf16_t* P = plds[w];
   for (int item = blockIdx.x * 4 + w; item < total; item += gridDim.x * 4) {
     const int wi = item / hkv, kvh = item - wi * hkv;
@@ -328,7 +335,7 @@ __global__ void __launch_bounds__(256) attn_bf16_kernel(AttnBf16Args A) {
     const int nch = (npg - skip_pages + A.chunk_pages - 1) / A.chunk_pages;
     const int pbeg = skip_pages + chunk * A.chunk_pages;
     const int pend = min(pbeg + A.chunk_pages, npg);
-    int nt_from = A.cs.nt_from;
+    int nt_from = nt_all;
     if (nt_from < 0 && pbeg < pend) {
       // not told: a chunk whose first page a neighbouring row lists at the same
       // place is taken to be shared (only the loads' cache policy depends on it)
@@ -1002,7 +1009,7 @@ hipError_t launch_attention_spec(const void* q, const void* k_pool, const void* 
   const int uni_nch = uniform ? ((min(cs.base, max_ctx) + cp * kPage - 1) / (cp * kPage)) : 0;
   if (!uniform)
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, st, cs, n_rows, cp * kPage,
-                       w.chunk_off, w.work, w.info);
+                       w.chunk_off, w.work, w.info, (int64_t)(kNtKvBytes / (4.0 * hkv * hd)));
   const int64_t maxch = uniform ? (int64_t)n_rows * uni_nch
                                 : (int64_t)n_rows * ((max_ctx + cp * kPage - 1) / (cp * kPage));
   const int64_t items = maxch * (bf16 ? hkv : hq);
@@ -1132,8 +1139,11 @@ hipError_t launch_attention(const void* q, const void* k_pool, const void* v_poo
   // stateless call's rows may share pages, which the kernel looks at, and below
   // the size of the Infinity Cache a caller that comes back with the same pools
   // finds them there (6 rows of 6000 keys: 25.9 us, non-temporal 28.0).
+  // (Ragged rows: by the sum of their contexts, on the device; 1024 rows of
+  // median 60 keys, 32/4 heads x 128, 173 MB under a bound of 3 GB, read again:
+  // 101 us, non-temporal 114.)
   const double kv_bytes = 4.0 * n_rows * hkv * hd * max_ctx;
-  cs.nt_from = row_pt ? shared_pages : kv_bytes >= 256e6 ? -1 : INT32_MAX;
+  cs.nt_from = row_pt ? shared_pages : kv_bytes >= kNtKvBytes ? -1 : INT32_MAX;
   cs.ctx_len = ctx_len; cs.mod = ctx_mod; cs.base = ctx_base; cs.row_pt = row_pt;
   cs.max_ctx = max_ctx; cs.n_pages = n_pages; cs.skip = 0; cs.pt_rows = 0;
   return launch_attention_spec(q, k_pool, v_pool, page_table, pt_stride, cs, n_rows, hq, hkv, hd,

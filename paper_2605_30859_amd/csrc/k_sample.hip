@@ -204,7 +204,6 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
   const int r = blockIdx.x / parts, part = blockIdx.x - r * parts;
   const int tid = threadIdx.x;
   if (tid == 0) s_thr = (int)0x807fffff;          // -INFINITY
-  __syncthreads();
   const RowCtx c = row_ctx<BF16, STATEFUL>(a, r);
   const int g = c.g, step = c.step;
   const uint32_t gc = (uint32_t)g + (uint32_t)a.traj_base;   // the counter's (global) trajectory id
@@ -226,9 +225,11 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
   auto block_thr = [&]() { return __hip_atomic_load(&s_thr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
   Raw4<BF16> next;
   if (jb + tid < je) next.load(row, jb + tid);
+  __syncthreads();                               // s_thr, while the first loads are under way
   for (int j = jb + tid; j < je; j += THREADS) {
     float z[4];
     next.get(z);
+    int known = block_thr();                     // read early; any earlier T is as sound
     if (j + THREADS < je) next.load(row, j + THREADS);
     if constexpr (TMODE != T_ONE) {
       constexpr float kBig = 1.2676506e+30f, kSmall = 7.8886091e-31f;   // 2^100, 2^-100
@@ -246,8 +247,10 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
       }
     }
     const Philox4 p = philox4x32_10((uint32_t)j, gc, (uint32_t)step, kTagSample, k0, k1);
-    float top = 0.f;     // largest of the elements' word + lim e^(z-m)
+    float word[4];       // the elements' word + lim e^(z-m)
+    float top = 0.f;     // the largest of them
     const float lm = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+    bool moved = false;
     if (lm > st.m) {
       if (st.s > 0.f) {   // rescale the running sums to the new maximum
         const float sc = __expf(st.m - lm);
@@ -255,10 +258,9 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
         st.s = st.s * sc;
       }
       st.m = lm;
-      set_lim();
+      moved = true;
       if (lm == INFINITY) top = 4294967296.0f;   // only the first infinite logit can win
     }
-    int known = block_thr();
     if (known == kNone) {
       // nothing seen yet: T from the fast scores of this group, less their error
       float f = -INFINITY;
@@ -268,8 +270,8 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
       if (f > -INFINITY) atomicMax(&s_thr, order_key(f));
       known = block_thr();
     }
-    if (known > thr) {
-      thr = known;
+    if (known > thr || moved) {
+      thr = max(thr, known);
       set_lim();
     }
 #pragma unroll
@@ -280,13 +282,25 @@ __global__ void __launch_bounds__(THREADS) sample_kernel(SampleArgs a) {
       const float ez = __expf(d);
       st.s += ez;
       st.t = fmaf(ez, d, st.t);
-      top = fmaxf(top, fmaf(ez, lim, (float)p.x[e]));
+      word[e] = fmaf(ez, lim, (float)p.x[e]);
     }
+    const float forced = top;
+    top = fmaxf(fmaxf(fmaxf(word[0], word[1]), fmaxf(word[2], word[3])), forced);
     if (top >= 4294967296.0f - kWordSlack) {
       const float before = best.v;
+      // the elements that pass, one at a time: early in a row every wavefront gets
+      // here, but mostly for one of a lane's four (a row of 4096 fp32 logits, four
+      // groups per lane: 7.1 us, with all four every time 8.0; evaluating the fast
+      // map for every element and the exact one once at the end: 6.4, which 200
+      // rows pay for with 16.2 against 9.2)
+      uint32_t pass = 0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float sc = z[e] + gumbel_of(open_unit(p.x[e]));
+      for (int e = 0; e < 4; ++e) pass |= (fmaxf(word[e], forced) >= 4294967296.0f - kWordSlack ? 1u : 0u) << e;
+#pragma unroll 1
+      for (; pass; pass &= pass - 1) {
+        const int e = __ffs(pass) - 1;
+        const uint32_t x = e == 0 ? p.x[0] : e == 1 ? p.x[1] : e == 2 ? p.x[2] : p.x[3];
+        const float sc = (e == 0 ? z[0] : e == 1 ? z[1] : e == 2 ? z[2] : z[3]) + gumbel_of(open_unit(x));
         if (sc > best.v) { best.v = sc; best.i = 4 * j + e; }
       }
       if (best.v > before) atomicMax(&s_thr, order_key(best.v));

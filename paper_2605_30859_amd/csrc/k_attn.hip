@@ -499,8 +499,8 @@ __global__ void __launch_bounds__(256) attn_prefix_kernel(AttnPrefixArgs A) {
 // as long as its products), hence two blocks per CU.  64 prompts x 512 tokens,
 // 32/4 heads x 128: 270 us per layer (137 GFLOP, 510 TFLOP/s), against 1600 us
 // for the decode kernel with one row per query position, which reads every key
-// once per query.  With 2 or 4 tiles per wavefront: 288 and 409 us (4 spill
-// past 256 registers); with the maximum moved on at every change: 286 us.
+// once per query.  With 2 or 4 tiles per wavefront instead of 3: 288 and 409 us
+// (4 spill past 256 registers; head dims 64 and 32 take 1 or 2); with the maximum moved on at every change: 286 us.
 struct PrefillArgs {
   const bf16_t* q; const bf16_t* kpool; const bf16_t* vpool;
   const int32_t* page_table; int64_t pt_step;   // page list of prompt i: page_table + i * pt_step
@@ -666,12 +666,21 @@ __global__ void __launch_bounds__(64 * kPreWaves, 2) attn_prefill_kernel(Prefill
   }
 }
 
+static int64_t prefill_blocks(const PrefillArgs& a, int nt) {
+  const int vecs = kPreWaves * nt * 16;
+  return ((int64_t)a.len * (a.hq / a.hkv) + vecs - 1) / vecs * a.n_prompts * a.hkv;
+}
 template <int HD, int NT>
 static void attn_prefill_go(const PrefillArgs& a, hipStream_t st) {
-  const int64_t tiles = ((int64_t)a.len * (a.hq / a.hkv) + kPreWaves * NT * 16 - 1) / (kPreWaves * NT * 16);
-  hipLaunchKernelGGL((attn_prefill_kernel<HD, NT>), dim3((unsigned)(tiles * a.n_prompts * a.hkv)), dim3(64 * kPreWaves),
-                     0, st, a);
+  hipLaunchKernelGGL((attn_prefill_kernel<HD, NT>), dim3((unsigned)prefill_blocks(a, NT)), dim3(64 * kPreWaves), 0, st,
+                     a);
 }
+// Head dims 64 and 32: two tiles per wavefront from so many blocks on, else one.
+// Prefill of six layers in 1 / 2 / 4 tiles: 16/4 heads x 64, 4 x 512 tokens 480 /
+// 512 / 561 us (512, 256 and 128 blocks), 8 x 512 624 / 640 / 688, 16 x 512 819 /
+// 808 / 859, 48 x 512 1606 / 1555 / 1630, 1 x 4096 974 / 1125 / 1504; 32/8 heads x
+// 32, 4 x 512 468 / 495 / 547, 8 x 512 629 / 628 / 672, 4 x 4096 2498 / 2382 / 2556.
+constexpr int64_t kPreBlocks2 = 1024;
 
 hipError_t launch_attention_prefill(const void* q, const void* k_pool, const void* v_pool, int64_t n_pages,
                                     const int32_t* page_table, int64_t pt_step, int n_prompts, int len, int hq,
@@ -683,8 +692,10 @@ hipError_t launch_attention_prefill(const void* q, const void* k_pool, const voi
   a.page_table = page_table; a.pt_step = pt_step; a.n_pages = n_pages;
   a.n_prompts = n_prompts; a.len = len; a.hq = hq; a.hkv = hkv; a.out = (bf16_t*)out;
   if (hd == 128) attn_prefill_go<128, 3>(a, st);
-  else if (hd == 64) attn_prefill_go<64, 4>(a, st);
-  else if (hd == 32) attn_prefill_go<32, 4>(a, st);
+  else if (hd == 64 && prefill_blocks(a, 2) >= kPreBlocks2) attn_prefill_go<64, 2>(a, st);
+  else if (hd == 64) attn_prefill_go<64, 1>(a, st);
+  else if (hd == 32 && prefill_blocks(a, 2) >= kPreBlocks2) attn_prefill_go<32, 2>(a, st);
+  else if (hd == 32) attn_prefill_go<32, 1>(a, st);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -491,16 +491,18 @@ __global__ void __launch_bounds__(256) attn_prefix_kernel(AttnPrefixArgs A) {
 //                                tile u is dim 8q + 4u + i, so that a lane ends
 //                                with 8 consecutive dims
 //   l              += 1 . P^T    the denominator: the sum of the rounded weights
-// The running maximum m is only moved on (and O and l rescaled) when a score
-// exceeds it by more than 8 in the exponent: weights then stay below 2^8, and
-// the ratio O / l is the same.
+// The running maximum m follows every score (O and l are rescaled), so that the
+// largest weight is 1, which bf16 holds exactly.  Letting m lag by up to 8 in the
+// exponent saves 7% of the time, but rounds that weight too: the weights'
+// share of the error grew from 7e-4 to 1.1e-3 of the result (head dim 128, 2048
+// keys, scores of a few units).
 //
 // Bound by VALU and matrix issue (the exponentials of a 16 x 32 tile take about
 // as long as its products), hence two blocks per CU.  64 prompts x 512 tokens,
-// 32/4 heads x 128: 270 us per layer (137 GFLOP, 510 TFLOP/s), against 1600 us
+// 32/4 heads x 128: 278 us per layer (137 GFLOP, 490 TFLOP/s), against 1600 us
 // for the decode kernel with one row per query position, which reads every key
-// once per query.  With 2 or 4 tiles per wavefront instead of 3: 288 and 409 us
-// (4 spill past 256 registers; head dims 64 and 32 take 1 or 2); with the maximum moved on at every change: 286 us.
+// once per query.  With 2 or 4 tiles per wavefront instead of 3: 7% and 50% more
+// (4 spill past 256 registers; head dims 64 and 32 take 1 or 2).
 struct PrefillArgs {
   const bf16_t* q; const bf16_t* kpool; const bf16_t* vpool;
   const int32_t* page_table; int64_t pt_step;   // page list of prompt i: page_table + i * pt_step
@@ -509,7 +511,6 @@ struct PrefillArgs {
   bf16_t* out;
 };
 constexpr int kPreWaves = 4, kPreKeys = 64;     // wavefronts per block (one copies one page), keys per stage
-constexpr float kPreLag = 8.0f;                 // how far (log2) scores may exceed the running maximum
 
 template <int HD, int NT>
 __global__ void __launch_bounds__(64 * kPreWaves, 2) attn_prefill_kernel(PrefillArgs A) {
@@ -624,7 +625,7 @@ __global__ void __launch_bounds__(64 * kPreWaves, 2) attn_prefill_kernel(Prefill
                          fmaxf(fmaxf(S[n][1][0], S[n][1][1]), fmaxf(S[n][1][2], S[n][1][3])));
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
-        if (__any(mx > m[n] + kPreLag)) {
+        if (__any(mx > m[n])) {
           const float mnew = fmaxf(m[n], mx);
           const float alpha = exp2f(m[n] - mnew);
           m[n] = mnew;

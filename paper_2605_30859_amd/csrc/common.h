@@ -113,7 +113,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Exclusive scan of one int per thread over a 1024-thread block: inclusive
 // scans inside each wavefront (shuffles), the 16 wavefront totals scanned by
-// the first wavefront through LDS, then added back.  sh holds >= 16 ints.
+// the first wavefront through LDS, then added back.  sh holds 32 ints.
 __device__ __forceinline__ int block_excl_scan1024(int v, int32_t* sh, int* total) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   int incl = v;

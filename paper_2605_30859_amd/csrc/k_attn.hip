@@ -300,8 +300,9 @@ __device__ __forceinline__ float row16_sum(float l) {
 // and the combine kernel merges them.  With a shared prefix the row's keys
 // start at cs.skip and chunk 0 starts from the prefix partials.
 //
-// Bound by HBM.  With uniform page ids and addresses (149 registers, 192 before)
-// and non-temporal loads of unshared pages: 777 rows x 1123 keys, 32/4 heads x
+// Bound by HBM.  Two wavefronts per SIMD (head dim 128: 149 vector and 32
+// accumulation registers; 160 and 32 when page ids and addresses were not scalar).
+// With scalar ids and non-temporal loads of unshared pages: 777 rows x 1123 keys, 32/4 heads x
 // 128: 300 us (6.0 TB/s), before 378; 1024 ragged rows, 32/8 heads: 1700 us,
 // before 1800; 512 rows of which 16 at a time share 32 of 57 pages: 196 us,
 // before 211.  Equal contiguous shares of all page pairs per wavefront, whatever

@@ -337,7 +337,8 @@ struct AltItem {
 // following one, or false.  nk: 64-wide K tiles of every item, even.  PW: W is
 // strip-packed (ldw = K).  An item's row list is read during the last K tiles of
 // the item before it, and its first loads are issued before that item's results
-// are stored, so neither latency is waited for.
+// are stored, so neither latency is waited for (EPI_ADD_F32 reads the results'
+// old values behind those loads, and waits for them).
 template <int BM, int BN, int WGM, int WGN, int EPI, bool SPLIT, bool PW, typename Next>
 __device__ __forceinline__ void alt_gemm_items(int lda, int ldw, int ldc, int nk, Next next) {
 #ifdef __HIP_DEVICE_COMPILE__   // the host pass knows no buffer resources
@@ -1415,8 +1416,8 @@ hipError_t launch_pack_strips(void* W, int64_t rows, int K, hipStream_t st) {
 // per expert: the prefill): 256x256 tiles of the alternating groups; gathered
 // rows beyond 32-bit offsets: 128x128 with a 4-stage ring, one block per CU.
 // Measured at 32768 rows of the Qwen3-30B-A3B experts, 256-row against 128-row
-// tiles: gate/up 1340 against 2450 us, down 904 against 1605 us; at 2928 rows
-// (183 per expert, 256-row tiles 71% full): see grouped_plan.  64-row tiles
+// tiles: gate/up 1340 against 2450 us, down 904 against 1605 us; down to 97
+// rows per expert: see GroupedPlan.  64-row tiles
 // (decode batches, where the expert weights are streamed): two blocks per
 // CU, so one block's loads stream while the other waits at its barrier or
 // refills its ring at an item boundary; 64x64 tiles with a 4-stage ring for

@@ -233,3 +233,25 @@ def test_swiglu_rows_do_not_depend_on_the_tile(M, kind, scale):
         torch.cuda.synchronize()
         same = whole[r0:r0 + part].view(torch.int16) == rows.view(torch.int16)
         assert bool(same.all()), (M, kind, scale, r0, int((~same).sum()))
+
+
+@pytest.mark.parametrize("M,epi", [(300, 1), (1100, 1), (300, 3), (1100, 3)])
+def test_gemm_16_bit_results_at_any_element(M, epi):
+    """16-bit results that start at an odd element: those of the large tiles are
+    stored 16 bytes at a time and have to lie where an aligned call's lie."""
+    print(f"gemm unaligned results M={M} epi={epi}", flush=True)
+    B = _b()
+    N, K = 24576, 512
+    assert B.darts_debug_gemm_plan(M, N, K, epi)[3:5] == (1, 1)
+    g = torch.Generator(device=DEV).manual_seed(M)
+    a = torch.randn(M, K, device=DEV, generator=g).bfloat16()
+    w = (torch.randn(N, K, device=DEV, generator=g) / K ** 0.5).bfloat16()
+    cols = N // 2 if epi == 3 else N
+    out = torch.empty(M * cols, dtype=torch.bfloat16, device=DEV)
+    B.darts_gemm(a, w, out, M, N, K, B.DARTS_BF16, epi)
+    for shift in (1, 2, 7):
+        buf = torch.full((M * cols + 16,), 3.0, dtype=torch.bfloat16, device=DEV)
+        B.darts_gemm(a, w, buf[shift:], M, N, K, B.DARTS_BF16, epi)
+        torch.cuda.synchronize()
+        assert bool((buf[shift:shift + M * cols] == out).all()), shift
+        assert bool((buf[:shift] == 3.0).all()) and bool((buf[shift + M * cols:] == 3.0).all()), shift

@@ -332,8 +332,8 @@ def test_attention_small_ragged(dtype, hq, hkv, hd):
 
 @pytest.mark.parametrize("rows,hq,hkv,hd,ctx", [
     (1, 32, 8, 128, 700),
-    (63, 32, 8, 128, 257),      # one row below the double-buffered form; odd page count
-    (64, 32, 8, 128, 257),      # the first double-buffered batch size
+    (63, 32, 8, 128, 257),      # odd page count
+    (64, 32, 8, 128, 257),      # the same, one row more
     (64, 32, 8, 128, 17),       # one page pair, one key in its second page
     (100, 32, 8, 128, 16),      # one page, no second page in the pair
     (130, 32, 8, 128, 4111),    # rows split into chunks, combine
@@ -341,14 +341,14 @@ def test_attention_small_ragged(dtype, hq, hkv, hd):
     (96, 16, 4, 64, 1500),
     (80, 8, 8, 128, 33),        # G = 1
     (72, 8, 2, 32, 600),
-    (256, 32, 4, 128, 1500),    # the MoE shape's heads (G = 8), double-buffered
+    (256, 32, 4, 128, 1500),    # the MoE shape's heads (G = 8)
     (20, 32, 4, 128, 3001),     # G = 8, few rows: context chunks and combine
 ])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_attention_equal_contexts(rows, hq, hkv, hd, ctx, dtype):
     """The equal-context form a decode step takes (no per-row contexts; in
-    bf16 the work is mapped arithmetically, with double-buffered page pairs
-    from 64 rows) against the oracle, on every row or a sample of them."""
+    bf16 the work is mapped arithmetically) against the oracle, on every row
+    or a sample of them."""
     say(f"attention equal contexts {dtype} rows={rows} hq={hq} hkv={hkv} hd={hd} ctx={ctx}")
     seed = 123
     c = np.full(rows, ctx, dtype=np.int64)
@@ -359,6 +359,50 @@ def test_attention_equal_contexts(rows, hq, hkv, hd, ctx, dtype):
         ref = OS.attention_row(r, ctx, pt[r], seed, hq, hkv, hd)
         err = np.max(np.abs(got[r] - ref))
         assert err <= tol * max(1.0, np.max(np.abs(ref))), (r, err)
+    assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("equal", [True, False])
+def test_attention_neighbours_that_share_pages(equal):
+    """A call of 256 MB of keys and values and more looks for pages that a
+    neighbouring row lists at the same place (their loads stay in the caches).
+    Rows here share their first 20 pages (0 and 1, the first row among them), 130
+    (5 to 9, past a ragged chunk's 128), a stretch in the middle (12 and 13), the
+    whole list (22 and 23, the last row among them), or nothing."""
+    say(f"attention shared neighbours equal={equal}")
+    B = _b()
+    rows, hq, hkv, hd, seed = 24, 32, 8, 128, 55
+    ctx = np.full(rows, 2805) if equal else 2640 + 17 * np.arange(rows)
+    if not equal:
+        ctx[3], ctx[11] = 40, 2048
+    assert 4 * hkv * hd * int(ctx.sum()) >= 256e6
+    pages = -(-ctx // 16)
+    n_pages, width = int(pages.sum()) + 3, int(pages.max())
+    rng = np.random.default_rng(seed)
+    perm, pt = rng.permutation(n_pages), np.zeros((rows, width), dtype=np.int32)
+    for r in range(rows):
+        pt[r, :pages[r]], perm = perm[:pages[r]], perm[pages[r]:]
+    pt[1, :20] = pt[0, :20]
+    pt[6:10, :130] = pt[5, :130]
+    pt[13, 30:70] = pt[12, 30:70]
+    pt[23, :pages[22]] = pt[22, :pages[22]]
+    q = torch.empty(rows * hq * hd, dtype=torch.bfloat16, device=DEV)
+    kp = torch.empty(n_pages * hkv * 16 * hd, dtype=torch.bfloat16, device=DEV)
+    vp = torch.empty_like(kp)
+    B.darts_fill_uniform(q, OS.T_Q, seed, B.DARTS_BF16)
+    B.darts_fill_kv_pool(kp, vp, n_pages, hkv, hd, seed, B.DARTS_BF16)
+    out = torch.zeros(rows * hq * hd, dtype=torch.bfloat16, device=DEV)
+    most = int(ctx.max())
+    ws = torch.empty(B.darts_attn_workspace_bytes(rows, hq, hkv, hd, most), dtype=torch.uint8, device=DEV)
+    ctxd = None if equal else torch.from_numpy(ctx.astype(np.int32)).to(DEV)
+    B.darts_attn_decode(q, kp, vp, n_pages, torch.from_numpy(pt).to(DEV), ctxd, hq, hkv, hd, most, B.DARTS_BF16, out,
+                        ws, n_rows=rows)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy().reshape(rows, hq, hd)
+    for r in (0, 1, 3, 5, 7, 9, 11, 13, 22, 23):
+        ref = OS.attention_row(r, int(ctx[r]), pt[r], seed, hq, hkv, hd)
+        err = np.max(np.abs(got[r] - ref))
+        assert err <= 2e-2 * max(1.0, np.max(np.abs(ref))), (r, ctx[r], err)
     assert np.isfinite(got).all()
 
 

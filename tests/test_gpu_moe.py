@@ -152,11 +152,11 @@ def test_moe_routing_extremes_teacher_forced(E, top_k, kv_fill):
 def test_moe_expert_kernel_paths_teacher_forced():
     """One rollout through every kernel path of the grouped expert GEMMs:
     16 experts top-4, 32 prompts x 8 trajectories, so the prefill has 256
-    routed rows per expert (128-row tiled tiles), the first decode steps
+    routed rows per expert (256-row tiles), the first decode steps
     51-64 (96-row gate/up tiles, weights straight into registers), the
     middle 4-46 (64-row, weights into registers) and the last steps 1.25
-    (64-row tiled tiles, strip-packed weights); down runs 128- and 64-row
-    tiled tiles.  The whole batch decodes on the GPU; prompt 0 and prompt 23
+    (64-row tiled tiles, strip-packed weights); down runs 256-row and 64-row
+    tiles.  The whole batch decodes on the GPU; prompt 0 and prompt 23
     (the last to complete) are teacher-forced with the oracle's tokens and
     experts (oracle.forced, computed here), and every row of theirs is
     compared as in the full-width test: logits at 256 ids, row max and
@@ -177,7 +177,7 @@ def test_moe_expert_kernel_paths_teacher_forced():
     E, k = model.n_experts, model.top_k
     per_expert = [int((length > s).sum()) * k / E for s in range(1, sched["steps"])]
     say(f"moe kernel paths: decode rows per expert {per_expert}")
-    assert run.n_prompts * run.prompt_len * k / E > 96          # the prefill's 128-row tiles
+    assert run.n_prompts * run.prompt_len * k / E > 96          # the prefill's 256-row tiles
     assert any(48 < x <= 96 for x in per_expert) and any(2 <= x <= 48 for x in per_expert)
     assert any(x < 2 for x in per_expert)
     last = int(np.argmax(sched["done_step"]))

@@ -1335,8 +1335,8 @@ static void dma_go(const Plan& p, const void* A, int lda, const void* W, int ldw
   }
 }
 
-// The ring kernel with a large tile of the alternating groups, for matrices
-// beyond those' 32-bit offsets.
+// The ring kernel with a large tile of the alternating groups, where those don't
+// run (plan_alternates).
 template <int EPI, int BM_, int BN_, int WGM, int WGN>
 static void dma_far(const Plan& p, const void* A, int lda, const void* W, int ldw, void* C, int ldc, int M, int N,
                     int K, void* ws, hipStream_t st) {
@@ -1352,16 +1352,34 @@ static void dma_far(const Plan& p, const void* A, int lda, const void* W, int ld
 static bool alt_reaches(int64_t lda, int64_t ldw, int64_t ldc, int esz) {
   return 256 * std::max(2 * std::max(lda, ldw), esz * ldc) < ((int64_t)1 << 31);
 }
-// Whether plan p runs on the alternating groups.  256x128 tiles with short K
-// ranges of a split do not: the three-stage ring has more of the weights in
-// flight from the first K tile on (QKV of the 8B shape at 256 rows in 4 splits:
-// 27.9 against 29.3 us); whole or long ranges alternate (gate/up at 2048 rows:
-// 349 against 382 us).
+// Whether plan p runs on the alternating groups.  Whole K mostly does; a split keeps the
+// ring kernel where it streams weights more than it computes (weights cold, ring
+// against alternating):
+//  * K ranges below 2048, but for 256x256 tiles of several row tiles: 12288 x 5120
+//    in 4 splits at 129-200 rows 42-49 / 48-55 us; QKV of the 8B shape
+//    in 4 splits at 256 rows 27.9 / 29.3, at 280 rows 34.4 / 38.4, at 340-400 rows
+//    38-40 / 38-40; 5120 x 12288 in 8 at 129-200 rows 49.5-54 / 51-57.  (256x256
+//    over two row tiles: down of the 8B shape in 8 splits at 300 rows 61 / 57.)
+//  * one row tile of weights on every CU: gate/up of the 8B shape in 2 splits at
+//    129-156 rows 63-66 / 69.  (On 192 CUs, 18432 x 4096, 55-61 / 51-57.)
+// Longer ranges alternate: 4096 x 12288 in 4 splits at 347-512 rows 62-65 / 56-65,
+// at 600-1000 rows 92-116 / 82-98; 8192 x 8192 in 2 at 640 rows 121 / 97.
+// Plain fp32 results of a short K are bound by their stores, which the blocks of
+// the ring kernel overlap better: K below 1024 (20480 x 512 at 129-256 rows 11.7-13.6
+// / 11.9-15.5, at 3000 rows 89 / 100; 16384 x 256 at 600 rows 14.5 / 17.2), below
+// 2048 up to 11 row tiles (151936 x 1024 at 256 rows 108 / 117; 1536 x 1024 at 3000
+// rows, 12 row tiles, 19.6 / 19.1), and 256x128 tiles of one row tile below K 3072
+// (151936 x 2048 at 183-256 rows 188-198 / 189-206; K 4096 349-355 / 320-342).
 static bool plan_alternates(const Plan& p, int lda, int ldw, int ldc, int N, int K, int epi) {
   if (p.kind < 3 || p.kind > 5) return false;
-  if (p.kind == 3 && p.S > 1 && K / p.S < 2048) return false;
-  if (p.S > 1) return alt_reaches(lda, ldw, N, 4);
-  return alt_reaches(lda, ldw, ldc, epi == EPI_BF16 || epi == EPI_SWIGLU ? 2 : 4);
+  if (p.S == 1) {
+    if (epi == EPI_F32 && (K < 2048 ? K < 1024 || p.mt < 12 : K < 3072 && p.mt == 1 && p.kind == 3))
+      return false;
+    return alt_reaches(lda, ldw, ldc, epi == EPI_BF16 || epi == EPI_SWIGLU ? 2 : 4);
+  }
+  if (K / p.S < 2048 && (p.kind != 4 || p.mt == 1)) return false;
+  if (K / p.S < 4096 && p.mt == 1 && p.nt * p.S >= kCus) return false;
+  return alt_reaches(lda, ldw, N, 4);
 }
 
 void gemm_plan_info(int M, int N, int K, int epi, int32_t* out) {

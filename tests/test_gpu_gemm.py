@@ -170,7 +170,7 @@ def test_gemm_f32_any_size(M, N, K, epi, shift):
     assert bool((out[M:] == 3.0).all())
 
 
-@pytest.mark.parametrize("M,N,K,epi", [(259, 4500096, 256, 0), (256, 4500096, 256, 2), (259, 8601600, 256, 1),
+@pytest.mark.parametrize("M,N,K,epi", [(259, 4500096, 2048, 0), (256, 4500096, 256, 2), (259, 8601600, 256, 1),
                                        (300, 256, 4 * 2 ** 21 + 2048, 0)])
 def test_gemm_rows_beyond_32_bit_offsets(M, N, K, epi):
     """Rows of C or of the operands so long that 256 of them pass 4 GiB: every

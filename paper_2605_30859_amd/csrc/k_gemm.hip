@@ -12,9 +12,10 @@
 //    share operand tiles in that XCD's L2.  Configs: 128x128 with 2 stages
 //    (64 KB, two blocks per CU: one block's barrier wait is covered by the
 //    other), 128x128 with 4 stages (one block per CU, deepest prefetch: for
-//    weight streaming over very wide N), 256x128 with 3 stages and 8 wavefronts
-//    (short K ranges), and 64- or 128-row tiles 64 or 96 wide with 4 stages
-//    for small batches, where they give exactly one block per CU.
+//    weight streaming over very wide N), 256x128 with 3 stages, 256x192 and
+//    256x256 with 2, all with 8 wavefronts (the large plans that the next family
+//    does not run, see plan_alternates), and 64- or 128-row tiles 64 or 96 wide
+//    with 4 stages for small batches, where they give exactly one block per CU.
 //  * alternating groups (large M): 256x128, 256x192 and 256x256 tiles on
 //    persistent blocks of 8 wavefronts in two groups, one fetching fragments
 //    while the other issues MFMAs.
@@ -1434,8 +1435,8 @@ hipError_t launch_pack_strips(void* W, int64_t rows, int K, hipStream_t st) {
 // per expert: the prefill): 256x256 tiles of the alternating groups; gathered
 // rows beyond 32-bit offsets: 128x128 with a 4-stage ring, one block per CU.
 // Measured at 32768 rows of the Qwen3-30B-A3B experts, 256-row against 128-row
-// tiles: gate/up 1340 against 2450 us, down 904 against 1605 us; down to 97
-// rows per expert: see GroupedPlan.  64-row tiles
+// tiles: gate/up 1395 against 2450 us, down 904 against 1605 us; from 97 rows per
+// expert: see GroupedPlan.  64-row tiles
 // (decode batches, where the expert weights are streamed): two blocks per
 // CU, so one block's loads stream while the other waits at its barrier or
 // refills its ring at an item boundary; 64x64 tiles with a 4-stage ring for
